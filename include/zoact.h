@@ -135,14 +135,18 @@ typedef struct {
                            ZOACT_SHARED_X (else ZOACT_E_UNSUPPORTED or INVALID)       */
   int64_t plain_end;
   void* ws;             /* optional workspace (16-byte aligned) of ws_bytes >=
-                           zoact_linear_workspace_bytes(): where the tiles leave a last
-                           round of the persistent grid at most half full (for example
-                           640 tiles on 256 compute units), BF16 plain or ReLU outputs
-                           without ZOACT_SHARED_X, the depth of that round's tiles is
-                           split over two workgroups and their halves summed (first +
-                           second) before the epilogue: other summation order, same
-                           bits in both halves of the pair.  NULL: not used.  Calls
-                           that overlap on one workspace race.                        */
+                           zoact_linear_workspace_bytes().  With BF16 activations the
+                           depth of a tile is split over several workgroups, whose fp32
+                           sums go here and are added in a fixed order before the
+                           epilogue, in two cases: few tokens, where whole-depth tiles
+                           would leave compute units idle (BF16 or INT4 weights with ch
+                           or r == 0, plain, ReLU or SwiGLU outputs; up to 16 slices,
+                           chosen by T, d_out, d_in and ws_bytes only); and a last round
+                           of the persistent grid at most half full (for example 640
+                           tiles on 256 compute units; BF16 weights, plain or ReLU
+                           outputs without ZOACT_SHARED_X; two slices).  Other summation
+                           order than without ws, same bits in both halves of the pair.
+                           NULL: not used.  Calls that overlap on one workspace race.    */
   size_t ws_bytes;
 } zoact_linear;
 

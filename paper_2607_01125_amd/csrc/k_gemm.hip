@@ -741,6 +741,7 @@ __global__ void __launch_bounds__(256) dequant_int4_kernel(const uint32_t* __res
 hipError_t launch_linear_pm_4w(const gemm::GemmArgs& a, int w_dtype, int epi, bool out_f32, hipStream_t s);
 hipError_t launch_linear_pm_4w64(const gemm::GemmArgs& a, int w_dtype, int epi, bool out_f32, bool shared,
                                  hipStream_t s);
+hipError_t launch_linear_pm_s(const gemm::GemmArgs& a, int w_dtype, int epi, bool out_f32, bool shared, hipStream_t s);
 
 // Arguments of the bf16-activation kernels for one call.
 static GemmArgs bf16_args(const zoact_linear& L, const zoact_arena* A, const void* x, int64_t T, const void* p,
@@ -813,6 +814,9 @@ hipError_t launch_linear_pm(const zoact_linear& L, const zoact_arena* A, const v
   const dim3 grid((unsigned)(2 * a.tiles_m_half * a.tiles_n));
   const bool i4 = L.w_dtype == ZOACT_INT4_G128;
   const bool of = y_dtype == ZOACT_F32;
+  // few tokens: the depth-split schedule
+  hipError_t e = launch_linear_pm_s(a, L.w_dtype, epi, of, (flags & ZOACT_SHARED_X) != 0, s);
+  if (e != hipErrorNotSupported) return e;
   // one half's x and p read by both halves: the 64-deep schedule's shared-input form only
   if (flags & ZOACT_SHARED_X) return launch_linear_pm_4w64(a, L.w_dtype, epi, of, true, s);
   // a plain feature range: the 64-deep schedule only
@@ -820,7 +824,7 @@ hipError_t launch_linear_pm(const zoact_linear& L, const zoact_arena* A, const v
   // the 64-deep persistent schedule where it applies (bf16 weights, C_h precomputed or
   // r = 0), else the 32-deep one (C_h formed in its prologue; INT4 in registers), else the
   // generic kernel (shapes outside both)
-  hipError_t e = launch_linear_pm_4w64(a, L.w_dtype, epi, of, false, s);
+  e = launch_linear_pm_4w64(a, L.w_dtype, epi, of, false, s);
   if (e != hipErrorNotSupported) return e;
   e = launch_linear_pm_4w(a, L.w_dtype, epi, of, s);
   if (e != hipErrorNotSupported) return e;
