@@ -88,12 +88,14 @@ zoact_status zoact_project(const void* x, int32_t dtype, int64_t n_tok, int64_t 
   if (dtype == ZOACT_BF16) {
     CHECK(d_in % 32 == 0, "project: bf16 needs d_in %% 32 == 0 (d_in=%lld)", (long long)d_in);
     CHECK(aligned16(x) && aligned16(ut), "project: x and ut must be 16-byte aligned");
+    const bool split = ws && r <= 64 && ws_bytes >= zoact::project_ws_bytes(n_tok, d_in, r) &&
+                       (d_in > 4096 || n_tok <= 4096);
+    if (split) CHECK(aligned16(ws), "project: ws must be 16-byte aligned");
+    const hipError_t few = zoact::launch_project_few(x, n_tok, d_in, ut, r, p, split ? ws : nullptr, st(stream));
+    if (few != hipErrorNotSupported) return hip_status(few, "project");
     // the depth-split form where it measured faster: deep inputs, or few tokens (at
     // 8192 x 4096 the single pass is level with it)
-    if (ws && r <= 64 && ws_bytes >= zoact::project_ws_bytes(n_tok, d_in, r) && (d_in > 4096 || n_tok <= 4096)) {
-      CHECK(aligned16(ws), "project: ws must be 16-byte aligned");
-      return hip_status(zoact::launch_project_split(x, n_tok, d_in, ut, r, p, ws, st(stream)), "project");
-    }
+    if (split) return hip_status(zoact::launch_project_split(x, n_tok, d_in, ut, r, p, ws, st(stream)), "project");
   }
   return hip_status(zoact::launch_project(x, dtype, n_tok, d_in, ut, r, p, st(stream)), "project");
 }

@@ -694,6 +694,89 @@ __global__ void __launch_bounds__(256) project_sum_kernel(const float* __restric
   }
 }
 
+// The same product for few tokens: 16 waves per workgroup share the depth of one 16 TB-token x
+// 16 CB-column tile, in units of 64 (a whole 128-byte line of each row) dealt round robin, so
+// that one short batch still has every wave's loads in flight; column tiles and, with a
+// workspace, up to four depth chunks give more workgroups.  Waves are added in a fixed order
+// through LDS (8 .. 15 onto 0 .. 7, then 0 .. 7).
+template <int TB, int CB>
+__global__ void __launch_bounds__(1024) project_few_kernel(const uint16_t* __restrict__ x,
+                                                           const uint16_t* __restrict__ ut, uint16_t* __restrict__ p,
+                                                           int64_t n_tok, int64_t d, int r, int64_t chunk,
+                                                           float* __restrict__ part) {
+  constexpr int TOK = 16 * TB, COL = 16 * CB;
+  __shared__ float red[8][TOK][COL + 1];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lr = lane & 15, lk = lane >> 4;
+  const int64_t t0 = (int64_t)blockIdx.x * TOK;
+  const int col0 = blockIdx.y * COL;
+  const int64_t k0 = (int64_t)blockIdx.z * chunk, k1 = k0 + chunk < d ? k0 + chunk : d;
+  const uint16_t* xr[TB];
+  const uint16_t* ur[CB];
+#pragma unroll
+  for (int i = 0; i < TB; ++i) {   // (rows past the ends repeat the last one; not stored)
+    const int64_t t = t0 + i * 16 + lr;
+    xr[i] = x + (t < n_tok ? t : n_tok - 1) * d + lk * 8;
+  }
+#pragma unroll
+  for (int j = 0; j < CB; ++j) {
+    const int c = col0 + j * 16 + lr;
+    ur[j] = ut + (int64_t)(c < r ? c : r - 1) * d + lk * 8;
+  }
+  floatx4 acc[TB][CB];
+#pragma unroll
+  for (int i = 0; i < TB; ++i)
+#pragma unroll
+    for (int j = 0; j < CB; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+  const bf16x8 zero8 = {};
+  for (int64_t k = k0 + wave * 64; k < k1; k += 2048) {   // two of this wave's units
+    bf16x8 a[4][TB], b[4][CB];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t ku = k + (u >> 1) * 1024 + (u & 1) * 32;
+      const bool in = ku < k1;
+#pragma unroll
+      for (int i = 0; i < TB; ++i) a[u][i] = in ? *reinterpret_cast<const bf16x8*>(xr[i] + ku) : zero8;
+#pragma unroll
+      for (int j = 0; j < CB; ++j) b[u][j] = in ? *reinterpret_cast<const bf16x8*>(ur[j] + ku) : zero8;
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int i = 0; i < TB; ++i)
+#pragma unroll
+        for (int j = 0; j < CB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[u][i], b[u][j], acc[i][j], 0, 0, 0);
+  }
+  if (wave >= 8) {
+#pragma unroll
+    for (int i = 0; i < TB; ++i)
+#pragma unroll
+      for (int j = 0; j < CB; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) red[wave - 8][i * 16 + lk * 4 + q][j * 16 + lr] = acc[i][j][q];
+  }
+  __syncthreads();
+  if (wave < 8) {
+#pragma unroll
+    for (int i = 0; i < TB; ++i)
+#pragma unroll
+      for (int j = 0; j < CB; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) red[wave][i * 16 + lk * 4 + q][j * 16 + lr] += acc[i][j][q];
+  }
+  __syncthreads();
+  const int e = threadIdx.x;
+  if (e >= TOK * COL) return;
+  const int tl = e / COL, c = e % COL;
+  const int64_t t = t0 + tl;
+  if (t >= n_tok || col0 + c >= r) return;
+  float v = red[0][tl][c];
+#pragma unroll
+  for (int w = 1; w < 8; ++w) v += red[w][tl][c];
+  if (part) part[((int64_t)blockIdx.z * n_tok + t) * r + col0 + c] = v;
+  else p[t * r + col0 + c] = f2bf(v);
+}
+
 __global__ void project_f32_kernel(const float* x, const float* ut, float* p, int64_t n_tok, int64_t d, int r) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_tok * r; i += (int64_t)gridDim.x * blockDim.x) {
     const int64_t t = i / r;
@@ -960,6 +1043,11 @@ size_t project_ws_bytes(int64_t n_tok, int64_t d_in, int32_t r) {
   return (size_t)project_nsplit(d_in) * (size_t)n_tok * (size_t)r * 4;
 }
 
+static void launch_project_sum(const float* part, int ns, int64_t n, uint16_t* p, hipStream_t s) {
+  const int vec = (n % 4 == 0) && (reinterpret_cast<uintptr_t>(p) % 8 == 0);
+  project_sum_kernel<<<dim3((unsigned)((n + 1023) / 1024)), dim3(256), 0, s>>>(part, ns, n, p, vec);
+}
+
 hipError_t launch_project_split(const void* x, int64_t n_tok, int64_t d_in, const void* ut, int32_t r, void* p,
                                 void* ws, hipStream_t s) {
   const int ns = project_nsplit(d_in);
@@ -978,9 +1066,47 @@ hipError_t launch_project_split(const void* x, int64_t n_tok, int64_t d_in, cons
   else if (rb <= 4) ZO_PS(4);
   else return hipErrorNotSupported;
 #undef ZO_PS
-  const int64_t n = n_tok * r;
-  const int vec = (n % 4 == 0) && (reinterpret_cast<uintptr_t>(p) % 8 == 0);
-  project_sum_kernel<<<dim3((unsigned)((n + 1023) / 1024)), dim3(256), 0, s>>>(part, ns, n, pp, vec);
+  launch_project_sum(part, ns, n_tok * r, pp, s);
+  return hipGetLastError();
+}
+
+// The few-token form, up to 2048 tokens; else, and where its tiles would fill the chip more
+// than once (more of them only share the L2 -> CU rate with larger tiles' fewer bytes),
+// hipErrorNotSupported.  With a workspace the depth goes in up to four chunks, by d_in alone, so
+// that P's bits do not depend on the tokens beside a row (a shared input is projected over half
+// the rows of the stacked one).  Kernel times at 512 tokens, chunks + sum against one pass:
+// d_in = 4096, r = 32: 4.8 + 2.3 against 9.8 us.  Whole calls at 32 to 2048 tokens against the
+// forms below (us): 14336: 11-19 (19-25), 20480 at r = 64: 13-44 (34-46); at 4096 tokens level
+// or slower.
+hipError_t launch_project_few(const void* x, int64_t n_tok, int64_t d_in, const void* ut, int32_t r, void* p,
+                              void* ws, hipStream_t s) {
+  if (n_tok > 2048) return hipErrorNotSupported;
+  const int ns = ws ? project_nsplit(d_in) : 1;
+  auto wgs = [&](int t, int c) -> int64_t {
+    return (n_tok + 16 * t - 1) / (16 * t) * ((r + 16 * c - 1) / (16 * c)) * ns;
+  };
+  // the smallest tile that fits one round of the chip (two for the largest, whose workgroups
+  // are short with the depth in chunks)
+  int tb = 1, cb = 1;
+  if (wgs(1, 1) > 256) {
+    cb = 2;
+    if (wgs(1, 2) > 256) {
+      tb = 2;
+      if (ns == 1 || wgs(2, 2) > 512) return hipErrorNotSupported;
+    }
+  }
+  const int64_t chunk = ((d_in + ns - 1) / ns + 63) / 64 * 64;
+  const dim3 grid((unsigned)((n_tok + 16 * tb - 1) / (16 * tb)), (unsigned)((r + 16 * cb - 1) / (16 * cb)), (unsigned)ns);
+  const auto* xx = static_cast<const uint16_t*>(x);
+  const auto* uu = static_cast<const uint16_t*>(ut);
+  auto* pp = static_cast<uint16_t*>(p);
+  float* part = ns > 1 ? static_cast<float*>(ws) : nullptr;
+#define ZO_PF(TB, CB) project_few_kernel<TB, CB><<<grid, dim3(1024), 0, s>>>(xx, uu, pp, n_tok, d_in, r, chunk, part)
+  if (tb == 1 && cb == 1) ZO_PF(1, 1);
+  else if (tb == 1) ZO_PF(1, 2);
+  else ZO_PF(2, 2);
+#undef ZO_PF
+  if (ns > 1) launch_project_sum(part, ns, n_tok * r, pp, s);
   return hipGetLastError();
 }
 

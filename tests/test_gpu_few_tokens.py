@@ -131,3 +131,26 @@ def test_few_tokens_small_workspace(ws_kb):
     Z.linear_fwd_pm(lay, None, x, T, None, y, Z.Pert(1, 1, 0, 1e-3))
     assert_bf16_close(host(y), (x.double() @ w.double().T).cpu().numpy(), what=f"ws {ws_kb} KB")
     assert np.all(guard[ws_kb * 1024:].cpu().numpy() == 0x5A), "written past the workspace"
+
+
+# token counts at the edges of 16- and 32-token tiles and on both sides of each tile choice
+# (one round of 256 workgroups), depths below one wave's unit, off the 1024-deep rounds and in
+# four chunks with a ragged last one, ranks off the 16-column tiles
+@pytest.mark.parametrize("n,d,r", [(1, 32, 1), (17, 96, 16), (33, 1056, 5), (512, 4096, 32), (1025, 4096, 33),
+                                   (2048, 4096, 32), (700, 8224, 64), (2047, 14336, 32), (100, 5120, 100),
+                                   (2049, 1024, 8)])
+@pytest.mark.parametrize("use_ws", [False, True])
+def test_project_few_tokens(n, d, r, use_ws):
+    announce("project few tokens", n, d, r, use_ws)
+    x, ut = _g(1, n, d), _g(2, r, d, std=1.0 / math.sqrt(d))
+    ws = torch.empty(max(Z.project_workspace_bytes(n, d, r), 16), dtype=torch.uint8, device=dev()) if use_ws else None
+    guard = torch.full((n + 2, r), 3.0, dtype=torch.bfloat16, device=dev())
+    p = guard[1:n + 1] if r % 8 == 0 else torch.empty(n, r, dtype=torch.bfloat16, device=dev())
+    Z.project(x, ut, p, ws)
+    assert_bf16_close(host(p), (x.double() @ ut.double().T).cpu().numpy(), what="project, few tokens")
+    assert torch.all(guard[0] == 3.0) and torch.all(guard[n + 1] == 3.0)
+    # a row's bits do not depend on the rows beside it while both calls are of this form
+    if 1 < n <= 1024 and r <= 64:
+        half = torch.empty(n // 2, r, dtype=torch.bfloat16, device=dev())
+        Z.project(x[:n // 2], ut, half, ws)
+        assert torch.equal(half.view(torch.int16), p[:n // 2].contiguous().view(torch.int16))
