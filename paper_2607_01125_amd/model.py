@@ -46,10 +46,11 @@ import torch
 from . import zoact as Z
 
 SITES = ("attn", "o", "mlp", "down")
-# widths covered by zoact_rmsnorm_project / zoact_layernorm_project, and the largest row
-# count at which the decoder uses them
-NORM_PROJECT_WIDTHS = (128, 256, 512, 1024, 2048, 4096, 5120)
-NORM_PROJECT_MAX_ROWS = 4096
+# widths and row counts at which the decoder forms a norm and its site's projection in one pass
+NORM_PROJECT_WIDTHS = (128, 256, 512, 1024, 2048, 4096)
+NORM_PROJECT_ROWS = (2049, 4096)
+# largest tokens per half at which INT4 layers run on their packed weights
+INT4_PACKED_MAX_TOKENS = 256
 
 
 @dataclass
@@ -168,19 +169,22 @@ class Decoder:
         self.shared_first = True
         # norms that feed an adapted site (attention and MLP inputs) also form the site's
         # projection P = x U in the same pass where the library covers the width and it is
-        # the faster form: up to NORM_PROJECT_MAX_ROWS rows (measured on MI355X at d = 4096,
-        # r = 32: 4096 rows 25.3 us fused against 29.4 us for the norm and the projection
-        # apart; 8192 rows 42.0 against 39.6 us -- the fused pass re-reads its 16-token
-        # rows from L2 or memory between the statistics and the projection, and the
-        # separate norm already runs near the memory rate)
-        self.fuse_norm_project = mode != "fp32" and self.r <= 128 and self.d in NORM_PROJECT_WIDTHS
+        # the faster form.  Kernel times on MI355X at d = 4096, r = 32 (RMSNorm), fused
+        # against norm + projection: 512 rows 19.6 against 11 us, 2048 rows 22.8 against
+        # 18.7, 4096 rows 24.8 against 27, 8192 rows 42 against 39.6: its workgroups of 16
+        # tokens each walk the whole of U^T and read their rows twice, which only pays while
+        # the norm alone leaves the chip part idle and the rows outgrow the few-token
+        # projection.  LayerNorm at d = 5120, r = 64 is slower fused throughout (39 against
+        # 14 us at 512 rows, 48.6 against 36 at 4096).
+        self.fuse_norm_project = mode != "fp32" and self.r <= 32 and self.d in NORM_PROJECT_WIDTHS
         # INT4 layers: True dequantises each layer once per forward into one bf16 buffer (the
-        # largest layer's size, allocated on first use) and runs the bf16 schedule; False
-        # keeps the INT4 GEMM that converts the packed weights in LDS.  The first is faster
-        # at every batch size measured on MI355X (Llama-3-8B shape, 256 to 4096 tokens per
-        # half: 24.8 vs 25.6 ms to 97.8 vs 109.3 ms per step): the INT4 GEMM converts each
-        # weight once per 256-token tile, the pass once per forward, and the GEMM then reads
-        # the bf16 copy mostly from the last-level cache.
+        # largest layer's size, allocated on first use) and runs the bf16 schedule, from more
+        # than INT4_PACKED_MAX_TOKENS tokens per half; False always keeps the GEMMs that read
+        # the packed weights.  The same bits either way.  Four Llama-3-8B projections of a
+        # layer on MI355X, packed against pass + bf16 GEMM: 128 us against 198 at 16 tokens
+        # per half, 208 / 281 at 128, 304 / 334 at 256, 530 / 492 at 512, 1580 / 1347 at
+        # 2048: the packed GEMMs convert every weight once per token tile, the pass once per
+        # forward, at 2.5 bytes moved per weight.
         self.int4_dequant = bool(int4_dequant)
         self._wdq = None
 
@@ -205,6 +209,9 @@ class Decoder:
 
     def _int4_dq(self, T: int) -> bool:
         """Whether a forward over T tokens per half runs its INT4 layers dequantised."""
+        return self._int4_can_dq() and T > INT4_PACKED_MAX_TOKENS
+
+    def _int4_can_dq(self) -> bool:
         return self.mode == "int4" and self.int4_dequant
 
     def _pack(self, W, int4_dequant=True):
@@ -303,7 +310,7 @@ class Decoder:
     def _norm_site(self, l, site, x, w, b, y, adapt, calibrate):
         """The norm of x into y, then the site's projection of y into P (U^T of the site, or
         None where it is not adapted); one fused pass where the library covers it."""
-        if (adapt and self.fuse_norm_project and x.shape[0] <= NORM_PROJECT_MAX_ROWS
+        if (adapt and self.fuse_norm_project and NORM_PROJECT_ROWS[0] <= x.shape[0] <= NORM_PROJECT_ROWS[1]
                 and (l, site) in self._adapted_sites):
             ut = self.ut.get((l, site))
             if ut is None:
@@ -326,7 +333,9 @@ class Decoder:
     def _apply(self, lin_blk, x, T, y, pert, site_ut, residual=None, flags=0, adapt=True):
         lin, blk = lin_blk
         B = self._cur
-        if lin.w.dtype == torch.uint8 and self._int4_dq(T):
+        # (at any T: a depth the packed schedules do not cover, and the shared-input form)
+        if lin.w.dtype == torch.uint8 and (self._int4_dq(T) or (self._int4_can_dq() and
+                                                                (lin.d_in < 256 or flags & Z.SHARED_X))):
             n = lin.d_out * lin.d_in
             if self._wdq is None or self._wdq.numel() < n:
                 n = max(n, max(l.d_out * l.d_in for P in self.layers for l, _ in
@@ -359,7 +368,7 @@ class Decoder:
         precomputed, 8 <= r <= 32 with r % 8 == 0, depth a multiple of 64, no SwiGLU."""
         lin, blk = lin_blk
         return (self.shared_first and self.act == torch.bfloat16 and blk is not None and site_ut is not None
-                and self._ch is not None and (lin.w.dtype == torch.bfloat16 or self._int4_dq(T))
+                and self._ch is not None and (lin.w.dtype == torch.bfloat16 or self._int4_can_dq())
                 and 8 <= self.r <= 32 and self.r % 8 == 0 and lin.d_in % 64 == 0 and lin.d_in >= 128
                 and lin.plain[0] == lin.plain[1])
 
