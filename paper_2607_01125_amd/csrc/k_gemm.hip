@@ -305,8 +305,10 @@ __global__ void __launch_bounds__(NTHR, 1) gemm_pm_kernel(GemmArgs a) {
 }
 
 // ------------------------------------------------------------------ fp32 path
-// Plain fp32 SIMT tile (64 x 64 outputs, 256 threads, 4 x 4 per thread) for the
-// fp32 mode of small models; the correction block is appended as extra depth.
+// fp32 mode of small models, on v_mfma_f32_16x16x4_f32 with the operands straight from global
+// memory (16 bytes per lane and 16-deep unit).  Every output is one chain of fused multiply-adds
+// in ascending depth (the instruction accumulates its four products in that order), the
+// correction appended as extra depth with C +/- eps Z formed in registers.
 struct GemmArgsF32 {
   const float* x;
   const float* w;
@@ -326,91 +328,167 @@ struct GemmArgsF32 {
   int32_t tiles_m_half;
 };
 
-// Column q of thread tx covers tile feature (tx/8)*32 + (tx%8)*2 + (q&1) + (q>>1)*16,
-// so each thread holds a gate row (q = 0, 1) and the up row 16 later (q = 2, 3) of the
-// interleaved gate|up layout.
-__device__ __forceinline__ int f32_col(int tx, int q) { return (tx >> 3) * 32 + (tx & 7) * 2 + (q & 1) + (q >> 1) * 16; }
+// Values of depth 4 lk + s in register s of lane (lr, lk) -> depth 4 s + lk: the transpose of a
+// 4 x 4 block over lane groups and registers.
+__device__ __forceinline__ void transpose4(floatx4& v) {
+  typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+  uint32_t r[4];
+#pragma unroll
+  for (int s = 0; s < 4; ++s) r[s] = __float_as_uint(v[s]);
+  const auto a = __builtin_amdgcn_permlane32_swap(r[0], r[2], false, false);
+  const auto b = __builtin_amdgcn_permlane32_swap(r[1], r[3], false, false);
+  const auto c = __builtin_amdgcn_permlane16_swap(a[0], b[0], false, false);
+  const auto d = __builtin_amdgcn_permlane16_swap(a[1], b[1], false, false);
+  v = floatx4{__uint_as_float(c[0]), __uint_as_float(c[1]), __uint_as_float(d[0]), __uint_as_float(d[1])};
+}
 
-template <int EPI>
-__global__ void __launch_bounds__(256) gemm_pm_f32_kernel(GemmArgsF32 a) {
-  __shared__ float xs[16][65];
-  __shared__ float wsh[16][65];
-  const int tm = blockIdx.y;
-  const int half = tm / a.tiles_m_half;
-  const int64_t m0 = (int64_t)(tm % a.tiles_m_half) * 64;
-  const int64_t n0 = (int64_t)blockIdx.x * 64;
+// A wave owns 16 MI tokens x 32 features; a workgroup's four waves lie along the tokens (MI = 1)
+// or 2 x 2 (MI = 2).  The small tile is for few tokens and features: 64 x 64 tiles of scalar
+// multiply-adds left all but 2 to 16 compute units idle at 512 rows x 128-256 features (20-38 us
+// a call; now 4-8), and the chain order above keeps their bits.
+template <int EPI, int MI>
+__global__ void __launch_bounds__(256) gemm_pm_f32_kernel(GemmArgsF32 a, int vec) {
+  constexpr int TN = MI == 1 ? 32 : 64;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lr = lane & 15, lk = lane >> 4;
+  const int half = (int)blockIdx.x / a.tiles_m_half;
+  const int64_t m0 = (int64_t)((int)blockIdx.x % a.tiles_m_half) * 64 + (MI == 1 ? wave * 16 : (wave >> 1) * 32);
+  const int64_t n0 = (int64_t)blockIdx.y * TN + (MI == 1 ? 0 : (wave & 1) * 32);
+  if (m0 >= a.T || n0 >= a.N) return;   // (no barrier below)
   const float* xh = a.x + (int64_t)half * a.T * a.K;
-  const float* ph = a.p ? a.p + (int64_t)half * a.T * a.r : nullptr;
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  float acc[4][4] = {};
-  const int64_t ktot = a.K + a.r;
-  for (int64_t k0 = 0; k0 < ktot; k0 += 16) {
-    for (int i = threadIdx.x; i < 16 * 64; i += 256) {
-      const int kk = i & 15, rr = i >> 4;
-      const int64_t k = k0 + kk;
-      const int64_t m = m0 + rr, n = n0 + rr;
-      float xv = 0.f, wv = 0.f;
-      if (k < a.K) {
-        if (m < a.T) xv = xh[m * a.K + k];
-        if (n < a.N) wv = a.w[n * a.K + k];
-      } else if (k < ktot) {
-        const int64_t i2 = k - a.K;
-        if (m < a.T) xv = ph[m * a.r + i2];
-        if (n < a.N) {
+  floatx4 acc[2][MI];
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int i = 0; i < MI; ++i) acc[j][i] = floatx4{0.f, 0.f, 0.f, 0.f};
+  // four consecutive values of a row from depth k (zeros past the row's end or the last row)
+  auto row4 = [&](const float* row, bool in, int64_t k) -> floatx4 {
+    floatx4 v = {0.f, 0.f, 0.f, 0.f};
+    if (!in) return v;
+    if (vec) {
+      if (k < a.K) v = *reinterpret_cast<const floatx4*>(row + k);
+    } else {
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+        if (k + s < a.K) v[s] = row[k + s];
+    }
+    return v;
+  };
+  auto step = [&](floatx4 (&w)[2], floatx4 (&x)[MI]) {   // one 16-deep unit
+#pragma unroll
+    for (int j = 0; j < 2; ++j) transpose4(w[j]);
+#pragma unroll
+    for (int i = 0; i < MI; ++i) transpose4(x[i]);
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int i = 0; i < MI; ++i) acc[j][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[j][s], x[i][s], acc[j][i], 0, 0, 0);
+  };
+  const float* wr[2];
+  const float* xr[MI];
+  bool wi[2], xi[MI];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    wi[j] = n0 + j * 16 + lr < a.N;
+    wr[j] = a.w + (wi[j] ? n0 + j * 16 + lr : 0) * a.K;
+  }
+#pragma unroll
+  for (int i = 0; i < MI; ++i) {
+    xi[i] = m0 + i * 16 + lr < a.T;
+    xr[i] = xh + (xi[i] ? m0 + i * 16 + lr : 0) * a.K;
+  }
+  const int64_t nu = (a.K + 15) >> 4;   // 16-deep units
+#pragma unroll 4
+  for (int64_t u = 0; u < nu; ++u) {
+    floatx4 w[2], x[MI];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) w[j] = row4(wr[j], wi[j], u * 16 + lk * 4);
+#pragma unroll
+    for (int i = 0; i < MI; ++i) x[i] = row4(xr[i], xi[i], u * 16 + lk * 4);
+    step(w, x);
+  }
+  if (a.r > 0) {
+    const float* ph = a.p + (int64_t)half * a.T * a.r;
+    const int sg = a.sign_h[half];
+    for (int t = 0; t < a.r; t += 16) {
+      const int i2 = t + lk * 4;
+      floatx4 w[2], x[MI];
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        w[j] = floatx4{0.f, 0.f, 0.f, 0.f};
+        if (!wi[j] || i2 >= a.r) continue;
+        const int64_t e = a.coef_offset + (n0 + j * 16 + lr) * a.r + i2;
+        const float4 z4 = gauss4(a.seed, a.step, a.query_h[half], (uint64_t)e);
+        const float z[4] = {z4.x, z4.y, z4.z, z4.w};
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
 #pragma clang fp contract(off)
-          const int64_t e = a.coef_offset + n * a.r + i2;
-          const float z = rng::gauss_at(a.seed, a.step, a.query_h[half], (uint64_t)e);
-          const float ez = a.eps * z;
-          const int sg = a.sign_h[half];
-          wv = sg > 0 ? a.c[e] + ez : (sg < 0 ? a.c[e] - ez : a.c[e]);
+          if (i2 + s >= a.r) continue;
+          const float ez = a.eps * z[s];
+          w[j][s] = sg > 0 ? a.c[e + s] + ez : (sg < 0 ? a.c[e + s] - ez : a.c[e + s]);
         }
       }
-      xs[kk][rr] = xv;
-      wsh[kk][rr] = wv;
-    }
-    __syncthreads();
 #pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-      float xr[4], wr[4];
+      for (int i = 0; i < MI; ++i) {
+        x[i] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        xr[q] = xs[kk][ty * 4 + q];
-        wr[q] = wsh[kk][f32_col(tx, q)];
+        for (int s = 0; s < 4; ++s)
+          if (xi[i] && i2 + s < a.r) x[i][s] = ph[(m0 + i * 16 + lr) * a.r + i2 + s];
       }
-#pragma unroll
-      for (int p = 0; p < 4; ++p)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) acc[p][q] += xr[p] * wr[q];
+      step(w, x);
     }
-    __syncthreads();
   }
+  // lane (lr, lk): features 4 lk .. +3 of each 16-feature block, token lr of each token block
   const int64_t nout = (EPI == ZOACT_EPI_SWIGLU) ? a.N / 2 : a.N;
-  for (int p = 0; p < 4; ++p) {
-    const int64_t m = m0 + ty * 4 + p;
+#pragma unroll
+  for (int i = 0; i < MI; ++i) {
+    const int64_t m = m0 + i * 16 + lr;
     if (m >= a.T) continue;
     const int64_t row = (int64_t)half * a.T + m;
-    if (EPI == ZOACT_EPI_SWIGLU) {
-      for (int q = 0; q < 2; ++q) {
-        const int64_t ng = n0 + f32_col(tx, q);
-        if (ng >= a.N) continue;
-        const float g = acc[p][q] + (a.bias ? a.bias[ng] : 0.f);
-        const float u = acc[p][q + 2] + (a.bias ? a.bias[ng + 16] : 0.f);
-        const int64_t f = (ng >> 5) * 16 + (ng & 31);
+    if constexpr (EPI == ZOACT_EPI_SWIGLU) {
+      if (n0 >= a.N) continue;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int64_t ng = n0 + lk * 4 + e, f = (n0 >> 5) * 16 + lk * 4 + e;
+        const float g = acc[0][i][e] + (a.bias ? a.bias[ng] : 0.f);
+        const float u = acc[1][i][e] + (a.bias ? a.bias[ng + 16] : 0.f);
         float o = (g / (1.0f + __expf(-g))) * u;
         if (a.resid) o += a.resid[row * nout + f];
         a.y[row * nout + f] = o;
       }
     } else {
-      for (int q = 0; q < 4; ++q) {
-        const int64_t n = n0 + f32_col(tx, q);
-        if (n >= a.N) continue;
-        float o = acc[p][q] + (a.bias ? a.bias[n] : 0.f);
-        if (a.resid) o += a.resid[row * nout + n];
-        if (EPI == ZOACT_EPI_RELU) o = fmaxf(o, 0.f);
-        a.y[row * nout + n] = o;
-      }
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int64_t n = n0 + j * 16 + lk * 4 + e;
+          if (n >= a.N) continue;
+          float o = acc[j][i][e] + (a.bias ? a.bias[n] : 0.f);
+          if (a.resid) o += a.resid[row * nout + n];
+          if (EPI == ZOACT_EPI_RELU) o = fmaxf(o, 0.f);
+          a.y[row * nout + n] = o;
+        }
     }
   }
+}
+
+// `halves` = 2: x [2][T][K]; 1: one set of rows (the projection).
+template <int EPI>
+hipError_t launch_f32(GemmArgsF32 a, int halves, hipStream_t s) {
+  // from two 64 x 64 tiles per compute unit the larger tiles (fewer operand bytes per product)
+  const int64_t tiles_m = (a.T + 63) / 64;
+  const bool small = tiles_m * halves * ((a.N + 63) / 64) < 512;
+  const int tn = small ? 32 : 64;
+  const int64_t tiles_n = (a.N + tn - 1) / tn;
+  if (tiles_m * halves > 0x7FFFFFFF || tiles_n > 65535) return hipErrorInvalidValue;
+  a.tiles_m_half = (int32_t)tiles_m;
+  const dim3 grid((unsigned)(tiles_m * halves), (unsigned)tiles_n);
+  const int vec = a.K % 4 == 0 && ((reinterpret_cast<uintptr_t>(a.x) | reinterpret_cast<uintptr_t>(a.w)) & 15) == 0;
+  if (small) gemm_pm_f32_kernel<EPI, 1><<<grid, dim3(256), 0, s>>>(a, vec);
+  else gemm_pm_f32_kernel<EPI, 2><<<grid, dim3(256), 0, s>>>(a, vec);
+  return hipGetLastError();
 }
 
 // ------------------------------------------------------------------ projection
@@ -777,16 +855,6 @@ __global__ void __launch_bounds__(1024) project_few_kernel(const uint16_t* __res
   else p[t * r + col0 + c] = f2bf(v);
 }
 
-__global__ void project_f32_kernel(const float* x, const float* ut, float* p, int64_t n_tok, int64_t d, int r) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_tok * r; i += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t t = i / r;
-    const int c = (int)(i % r);
-    float s = 0.f;
-    for (int64_t k = 0; k < d; ++k) s += x[t * d + k] * ut[(int64_t)c * d + k];
-    p[i] = s;
-  }
-}
-
 template <bool INT4, int EPI, bool OUT_F32>
 hipError_t launch_bf16(const GemmArgs& a, dim3 grid, hipStream_t s) {
   const size_t lds = (size_t)2 * (BN + BM) * BK * sizeof(uint16_t);
@@ -883,14 +951,11 @@ hipError_t launch_linear_pm(const zoact_linear& L, const zoact_arena* A, const v
     a.step = pert.step;
     for (int h = 0; h < 2; ++h) a.query_h[h] = pert.query[h], a.sign_h[h] = pert.sign[h];
     a.eps = pert.eps;
-    a.tiles_m_half = (int32_t)((T + 63) / 64);
-    dim3 grid((unsigned)((L.d_out + 63) / 64), (unsigned)(2 * a.tiles_m_half));
     a.resid = static_cast<const float*>(residual);
     a.y = static_cast<float*>(y);
-    if (epi == ZOACT_EPI_SWIGLU) gemm_pm_f32_kernel<ZOACT_EPI_SWIGLU><<<grid, dim3(256), 0, s>>>(a);
-    else if (epi == ZOACT_EPI_RELU) gemm_pm_f32_kernel<ZOACT_EPI_RELU><<<grid, dim3(256), 0, s>>>(a);
-    else gemm_pm_f32_kernel<0><<<grid, dim3(256), 0, s>>>(a);
-    return hipGetLastError();
+    if (epi == ZOACT_EPI_SWIGLU) return launch_f32<ZOACT_EPI_SWIGLU>(a, 2, s);
+    if (epi == ZOACT_EPI_RELU) return launch_f32<ZOACT_EPI_RELU>(a, 2, s);
+    return launch_f32<0>(a, 2, s);
   }
 
   GemmArgs a = bf16_args(L, A, x, T, p, residual, pert, y);
@@ -1113,12 +1178,14 @@ hipError_t launch_project_few(const void* x, int64_t n_tok, int64_t d_in, const 
 hipError_t launch_project(const void* x, int32_t dtype, int64_t n_tok, int64_t d_in, const void* ut, int32_t r, void* p,
                           hipStream_t s) {
   if (dtype == ZOACT_F32) {
-    int64_t g = (n_tok * r + 255) / 256;
-    if (g > 65535) g = 65535;
-    project_f32_kernel<<<dim3((unsigned)g), dim3(256), 0, s>>>(static_cast<const float*>(x),
-                                                               static_cast<const float*>(ut), static_cast<float*>(p),
-                                                               n_tok, d_in, r);
-    return hipGetLastError();
+    GemmArgsF32 a{};   // a plain product with U^T as the weight
+    a.x = static_cast<const float*>(x);
+    a.w = static_cast<const float*>(ut);
+    a.y = static_cast<float*>(p);
+    a.T = n_tok;
+    a.N = r;
+    a.K = d_in;
+    return launch_f32<0>(a, 1, s);
   }
   // 32 tokens per workgroup (two 16-token blocks per wave): fewer would multiply the U^T
   // reads per token
