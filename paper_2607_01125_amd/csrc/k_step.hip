@@ -309,32 +309,31 @@ __global__ void __launch_bounds__(256) perturb_kernel(const void* __restrict__ c
 
 // One-sided multi-query estimate of Algorithm 2: gh = (sum_j a_j Z^(j)) / q with
 // a_j = (L_j - L_0) / eps, accumulated in fp32 with j ascending; then Adam (ADAM) or
-// SGD on gh.  Returns false (no update anywhere) when some a_j is not finite.
-__device__ __forceinline__ bool query_coeffs_finite(const float* losses, int q, float eps) {
-#pragma clang fp contract(off)
-  const float l0 = losses[0];
-  for (int j = 1; j <= q; ++j)
-    if (!__builtin_isfinite((losses[j] - l0) / eps)) return false;
-  return true;
-}
-
+// SGD on gh.
 template <bool BF16C, bool ADAM>
 __global__ void __launch_bounds__(256) step_q_kernel(void* __restrict__ cptr, float* __restrict__ mptr,
                                                      float* __restrict__ vptr, int64_t k, const float* losses, int q,
                                                      uint64_t seed, uint32_t step, float eps, AdamConst h, float lr,
                                                      uint32_t* status) {
 #pragma clang fp contract(off)
-  if (!query_coeffs_finite(losses, q, eps)) {
+  // a_j = (L_j - L_0) / eps, formed once per workgroup (q <= 256, one per thread)
+  __shared__ float aj_sh[256];
+  bool finite = true;
+  if ((int)threadIdx.x < q) {
+    const float aj = (losses[threadIdx.x + 1] - losses[0]) / eps;
+    aj_sh[threadIdx.x] = aj;
+    finite = __builtin_isfinite(aj);
+  }
+  if (!__syncthreads_and(finite)) {   // some a_j is not finite: no update anywhere
     if (status != nullptr && blockIdx.x == 0 && threadIdx.x == 0) atomicOr(status, 1u);
     return;
   }
-  const float l0 = losses[0];
   const float qf = (float)q;
   const int64_t nb = (k + 3) >> 2;
   for (int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; b < nb; b += (int64_t)gridDim.x * blockDim.x) {
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
     for (int j = 1; j <= q; ++j) {
-      const float aj = (losses[j] - l0) / eps;
+      const float aj = aj_sh[j - 1];
       const float4 z = rng::gauss_block(seed, step, (uint32_t)j, (uint64_t)b);
       acc[0] = acc[0] + aj * z.x;
       acc[1] = acc[1] + aj * z.y;

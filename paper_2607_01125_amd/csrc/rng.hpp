@@ -12,8 +12,13 @@
 //     R = sqrt(-2 ln u1); quadrant w1 >> 30 and 22 fraction bits f, with
 //     sin(pi f/2), cos(pi f/2) from Maclaurin series of degree 13 and 14.
 // Every step is one fp32 operation in the written order: no contraction into
-// fused multiply-adds, IEEE correctly rounded division and square root, so the
+// fused multiply-adds, correctly rounded division and square root, so the
 // values are reproducible bit for bit by any IEEE fp32 implementation.
+//
+// Where a kernel draws several values per coefficient (the q-query update) the generator's
+// instructions bound it.  One 64-bit product per Philox multiply, the short division and square
+// root below and sign flips instead of selects: 150 -> 114 us for 8 queries over
+// 11,010,048 coefficients (with the a_j formed once per workgroup), same bits.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -33,19 +38,36 @@ __device__ __forceinline__ Words philox4x32_10(uint32_t c0, uint32_t c1, uint32_
       k0 += 0x9E3779B9u;  // Weyl increments of the key schedule
       k1 += 0xBB67AE85u;
     }
-    const uint32_t hi0 = __umulhi(0xD2511F53u, c0), lo0 = 0xD2511F53u * c0;
-    const uint32_t hi1 = __umulhi(0xCD9E8D57u, c2), lo1 = 0xCD9E8D57u * c2;
-    const uint32_t n0 = hi1 ^ c1 ^ k0;
-    const uint32_t n2 = hi0 ^ c3 ^ k1;
+    // (both halves of a product from one 32 x 32 -> 64 multiply)
+    const uint64_t p0 = (uint64_t)0xD2511F53u * c0, p1 = (uint64_t)0xCD9E8D57u * c2;
+    const uint32_t n0 = (uint32_t)(p1 >> 32) ^ c1 ^ k0;
+    const uint32_t n2 = (uint32_t)(p0 >> 32) ^ c3 ^ k1;
     c0 = n0;
-    c1 = lo1;
+    c1 = (uint32_t)p1;
     c2 = n2;
-    c3 = lo0;
+    c3 = (uint32_t)p0;
   }
   return Words{c0, c1, c2, c3};
 }
 
 __device__ __forceinline__ float f32_bits(uint32_t b) { return __uint_as_float(b); }
+
+// n / d and sqrt(x) for this generator's operands, correctly rounded without the range scaling
+// and special cases of the general forms: a reciprocal (square root) estimate, one refinement,
+// and one step on the exact residual.  d is in [1.7, 2.5) and |n| < 0.42; x is 0 (of either sign,
+// returned as it is) or in [1e-7, 34).  Both depend only on the 24 bits of a uniform: the results
+// equal the IEEE operations' for all 2^24 of them (checked on the device).
+__device__ __forceinline__ float div_small(float n, float d) {
+  float r = __builtin_amdgcn_rcpf(d);
+  r = __builtin_fmaf(__builtin_fmaf(-d, r, 1.0f), r, r);
+  const float q = n * r;
+  return __builtin_fmaf(__builtin_fmaf(-d, q, n), r, q);
+}
+__device__ __forceinline__ float sqrt_small(float x) {
+  const float y = __builtin_amdgcn_rsqf(fmaxf(x, 0x1p-60f));
+  const float g = x * y;
+  return __builtin_fmaf(__builtin_fmaf(-g, g, x), 0.5f * y, g);
+}
 
 // ln(((w >> 8) + 1) * 2^-24) via exponent split and the atanh series.
 __device__ __forceinline__ float log_uniform(uint32_t w) {
@@ -58,7 +80,7 @@ __device__ __forceinline__ float log_uniform(uint32_t w) {
     m = m * 0.5f;
     e += 1;
   }
-  const float s = (m - 1.0f) / (m + 1.0f);
+  const float s = div_small(m - 1.0f, m + 1.0f);
   const float s2 = s * s;
   float p = f32_bits(0x3DE38E39u);   // 1/9
   p = p * s2 + f32_bits(0x3E124925u);  // 1/7
@@ -72,7 +94,6 @@ __device__ __forceinline__ float log_uniform(uint32_t w) {
 // (cos, sin) of the quarter-turn angle (w >> 30) + f, f = ((w >> 8) & 0x3FFFFF) 2^-22.
 __device__ __forceinline__ void quarter_turn_sincos(uint32_t w, float& c_out, float& s_out) {
 #pragma clang fp contract(off)
-  const uint32_t q = w >> 30;
   const float f = (float)((w >> 8) & 0x3FFFFFu) * 0x1p-22f;
   const float f2 = f * f;
   // (pi/2)^n / n! with alternating signs, rounded to fp32
@@ -93,13 +114,16 @@ __device__ __forceinline__ void quarter_turn_sincos(uint32_t w, float& c_out, fl
   cp = cp * f2 + f32_bits(0xBF9DE9E6u);  // - x^2
   cp = cp * f2 + 1.0f;
   const float cs = cp;
-  c_out = (q == 0) ? cs : (q == 1) ? -sn : (q == 2) ? -cs : sn;
-  s_out = (q == 0) ? sn : (q == 1) ? cs : (q == 2) ? -sn : -cs;
+  // quadrant q: (c, s) = (cs, sn), (-sn, cs), (-cs, -sn), (sn, -cs): swapped when q is odd; s
+  // negative in quadrants 2 and 3 (bit 31 of w), c in 1 and 2 (bit 31 of w plus a quarter turn)
+  const bool odd = (w & 0x40000000u) != 0;
+  c_out = f32_bits(__float_as_uint(odd ? sn : cs) ^ ((w + 0x40000000u) & 0x80000000u));
+  s_out = f32_bits(__float_as_uint(odd ? cs : sn) ^ (w & 0x80000000u));
 }
 
 __device__ __forceinline__ void box_muller(uint32_t wa, uint32_t wb, float& z0, float& z1) {
 #pragma clang fp contract(off)
-  const float rad = __builtin_sqrtf(-2.0f * log_uniform(wa));
+  const float rad = sqrt_small(-2.0f * log_uniform(wa));
   float c, s;
   quarter_turn_sincos(wb, c, s);
   z0 = rad * c;
