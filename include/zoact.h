@@ -141,10 +141,11 @@ typedef struct {
                            epilogue, in two cases: few tokens, where whole-depth tiles
                            would leave compute units idle (BF16 or INT4 weights with ch
                            or r == 0, plain, ReLU or SwiGLU outputs; up to 16 slices,
-                           chosen by T, d_out, d_in and ws_bytes only); and a last round
-                           of the persistent grid at most half full (for example 640
-                           tiles on 256 compute units; BF16 weights, plain or ReLU
-                           outputs without ZOACT_SHARED_X; two slices).  Other summation
+                           chosen by T, d_out, d_in and ws_bytes only); and a last, partly
+                           idle round of the persistent grid, or one launch of fewer
+                           tiles than compute units, spread over them by depth where that
+                           is faster (for example 160 or 640 tiles on 256 compute units;
+                           BF16 weights without ZOACT_SHARED_X).  Other summation
                            order than without ws, same bits in both halves of the pair.
                            NULL: not used.  Calls that overlap on one workspace race.    */
   size_t ws_bytes;
@@ -277,8 +278,8 @@ zoact_status zoact_linear_fwd_pair(const zoact_linear* L, const zoact_arena* A, 
                                    uint32_t flags, const zoact_pert_pair* pp, void* y, int32_t y_dtype,
                                    zoact_stream stream);
 
-/* Bytes of the optional zoact_linear workspace on the current device (one 256 KB tile
- * slot per compute unit). */
+/* Bytes of the optional zoact_linear workspace on the current device (two 256 KB tile
+ * slots per compute unit; a smaller one is used as far as it goes). */
 size_t zoact_linear_workspace_bytes(void);
 
 /* INT4 weights to bf16: out[n][k] = bf16(q[n][k] * s[n][k / 128]), the dequantised weight
@@ -331,7 +332,9 @@ size_t zoact_loss_workspace_bytes(void);
  * logit; a second pass merges the blocks per row (the online log-sum-exp rule) and sums
  * the rows in a fixed order.  x [2][B*S][d_in] bf16, tokens int32 [B][S] shared by both
  * halves (ids clamped to [0, d_out)), S >= 2.  BF16 activations and weights.
- * ws: zoact_linear_xent_workspace_bytes(B*S, d_out) bytes, 16-byte aligned.
+ * ws: zoact_linear_xent_workspace_bytes(B*S, d_out) bytes, 16-byte aligned; its last part
+ * holds the partial sums of a partly idle last round and may be left out (ws_bytes smaller
+ * by up to 512 KB per compute unit: that round then runs whole tiles).
  * Errors: shapes the fused kernel does not cover -> ZOACT_E_UNSUPPORTED. */
 size_t zoact_linear_xent_workspace_bytes(int64_t T, int64_t d_out);
 zoact_status zoact_linear_xent_pair(const zoact_linear* L, const zoact_arena* A, const void* x, int64_t B, int64_t S,

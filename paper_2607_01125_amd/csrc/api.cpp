@@ -102,7 +102,7 @@ zoact_status zoact_project(const void* x, int32_t dtype, int64_t n_tok, int64_t 
 
 size_t zoact_linear_workspace_bytes(void) {
   const int n = zoact::cu_count();
-  return n > 0 ? (size_t)n * 256 * 1024 : 0;
+  return n > 0 ? (size_t)n * 512 * 1024 : 0;
 }
 
 zoact_status zoact_dequant_int4(const void* w, const void* w_scales, int64_t d_out, int64_t d_in, void* out,
@@ -260,7 +260,8 @@ zoact_status zoact_mse_pm(const void* y, int32_t dtype, const void* target, int6
 
 size_t zoact_linear_xent_workspace_bytes(int64_t T, int64_t d_out) {
   if (T < 1 || d_out < 1) return 0;
-  return zoact::linear_xent_ws_bytes(T, d_out);
+  // the loss's own buffers, then the slots of the GEMM's split tail (used where given)
+  return ((zoact::linear_xent_ws_bytes(T, d_out) + 255) & ~(size_t)255) + zoact::tail_ws_bytes(T, d_out);
 }
 
 zoact_status zoact_linear_xent_pair(const zoact_linear* L, const zoact_arena* A, const void* x, int64_t B, int64_t S,
@@ -272,10 +273,10 @@ zoact_status zoact_linear_xent_pair(const zoact_linear* L, const zoact_arena* A,
   // the shared validation of the layer, with x standing in for the unused output
   const zoact_status v = validate_linear(L, A, x, ZOACT_BF16, B * S, p, nullptr, 0, pp, x, ZOACT_F32);
   if (v != ZOACT_OK) return v;
-  const size_t need = zoact_linear_xent_workspace_bytes(B * S, L->d_out);
+  const size_t need = zoact::linear_xent_ws_bytes(B * S, L->d_out);
   if (ws == nullptr || ws_bytes < need || !aligned16(ws))
     return fail(ZOACT_E_WORKSPACE, "linear_xent: workspace needs %zu bytes, 16-byte aligned", need);
-  return hip_status(zoact::launch_linear_xent(*L, A, x, B * S, p, *pp, tokens, S, loss_pm, ws, st(stream)),
+  return hip_status(zoact::launch_linear_xent(*L, A, x, B * S, p, *pp, tokens, S, loss_pm, ws, ws_bytes, st(stream)),
                     "linear_xent");
 }
 

@@ -717,5 +717,115 @@ __device__ __forceinline__ void epilogue_regs(const GemmArgs& a, floatx4 (&acc)[
   else epilogue_regs_impl<EPI, OUT_F32, false, CORR>(a, acc, tq, wave, lane, m0, n0, half, tm, tn);
 }
 
+// The epilogue of one token block of a wave: NI 16-feature blocks of accumulators, token
+// (half, t), first feature nw.  The operations and their order are those of the
+// register epilogue.
+template <int EPI, bool OUT_F32, int NI>
+__device__ __forceinline__ void emit(const GemmArgs& a, const floatx4 (&v)[NI], int half, int64_t t, int64_t nw,
+                                     int lk) {
+  if (t >= a.T) return;
+  const int64_t row = (int64_t)half * a.T + t;
+  if constexpr (EPI == ZOACT_EPI_SWIGLU) {
+    const int64_t nout = a.N / 2;
+#pragma unroll
+    for (int q = 0; q < NI / 2; ++q) {
+      const int64_t ng = nw + q * 32 + lk * 4, no = nw / 2 + q * 16 + lk * 4;
+      if (nw + q * 32 >= a.N) continue;
+      float g[4], u[4], o[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) g[e] = v[2 * q][e], u[e] = v[2 * q + 1][e];
+      if (a.bias) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) g[e] += bf2f(a.bias[ng + e]), u[e] += bf2f(a.bias[ng + 16 + e]);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] = silu(g[e]) * u[e];
+      if (a.resid) {
+        const uint2 rv = *reinterpret_cast<const uint2*>(a.resid + row * nout + no);
+        o[0] += bf_lo(rv.x), o[1] += bf_hi(rv.x), o[2] += bf_lo(rv.y), o[3] += bf_hi(rv.y);
+      }
+      *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.y) + row * nout + no) =
+          make_uint2(pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3]));
+    }
+  } else {
+#pragma unroll
+    for (int q = 0; q < NI / 2; ++q) {
+      const int64_t n = nw + q * 32 + lk * 8;
+      if (n >= a.N) continue;
+      float o[8];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] = v[2 * q][e], o[4 + e] = v[2 * q + 1][e];
+      if (a.bias) {   // (its alignment is not part of the contract)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[e] += bf2f(a.bias[n + e]);
+      }
+      if (a.resid) {
+        const uint4 rv = *reinterpret_cast<const uint4*>(a.resid + row * a.N + n);
+        const uint32_t w[4] = {rv.x, rv.y, rv.z, rv.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[2 * e] += bf_lo(w[e]), o[2 * e + 1] += bf_hi(w[e]);
+      }
+      if (EPI == ZOACT_EPI_RELU) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[e] = fmaxf(o[e], 0.0f);
+      }
+      if (OUT_F32) {
+        float* yp = reinterpret_cast<float*>(a.y) + row * a.N + n;
+        *reinterpret_cast<float4*>(yp) = make_float4(o[0], o[1], o[2], o[3]);
+        *reinterpret_cast<float4*>(yp + 4) = make_float4(o[4], o[5], o[6], o[7]);
+      } else {
+        *reinterpret_cast<uint4*>(reinterpret_cast<uint16_t*>(a.y) + row * a.N + n) =
+            make_uint4(pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3]), pack_bf16x2(o[4], o[5]),
+                       pack_bf16x2(o[6], o[7]));
+      }
+    }
+  }
+}
+
+// The cross entropy of one token block of a wave from stored accumulators: 8 16-feature blocks
+// of token (half, t), first feature nw.  The operations and their order are those of the
+// register epilogue.
+__device__ __forceinline__ void emit_xent(const GemmArgs& a, const floatx4 (&c)[8], int half, int64_t t, int64_t nw,
+                                          int lane) {
+  const int lk = lane >> 4, seq = (int)a.seq;
+  const bool mv = t < a.T;
+  int nxt = -1;
+  if (mv && (int)t % seq < seq - 1) {
+    const int k = a.tok[t + 1];
+    nxt = k < 0 ? 0 : (k >= a.N ? (int)a.N - 1 : k);
+  }
+  float v[8][4], mx = -INFINITY;
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      v[i][e] = c[i][e];
+      if (a.bias && nw + i * 16 < a.N) v[i][e] += bf2f(a.bias[nw + i * 16 + lk * 4 + e]);
+      if (nw + i * 16 < a.N) mx = fmaxf(mx, v[i][e]);
+    }
+  mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+  mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+  const int64_t row = (int64_t)half * a.T + t;
+  const int d = nxt - (int)nw;   // the next token's offset in this block
+  if (mv && nxt >= 0 && d >= 0 && d < 128 && ((d >> 2) & 3) == lk) {
+    float tv = 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (d == i * 16 + lk * 4 + e) tv = v[i][e];
+    a.xtgt[row] = tv;
+  }
+  float sp[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) sp[e] += nw + i * 16 < a.N ? __expf(v[i][e] - mx) : 0.f;
+  float se = (sp[0] + sp[1]) + (sp[2] + sp[3]);
+  se += __shfl_xor(se, 16, 64);
+  se += __shfl_xor(se, 32, 64);
+  if (mv && lk == 0 && nw < a.N) a.xpart[row * a.xnblk + (nw >> 7)] = make_float2(mx, se);
+}
+
 }  // namespace gemm
 }  // namespace zoact

@@ -38,10 +38,12 @@ struct GemmArgs {
   int32_t xnblk;         // EPI_XENT: ceil(N / 128)
   int64_t plain_begin;   // output features [plain_begin, plain_end): no correction, no coefficient rows
   int64_t plain_end;
-  float* tail_ws;        // split tail (64-deep schedule): the half tiles' fp32 accumulators
+  float* tail_ws;        // fp32 accumulators of tiles split by depth
   int64_t tail_ws_bytes;
-  int32_t tail_first;    // first virtual tile that is half a tile (= the tile count: none)
+  int32_t tail_first;    // split tail (64-deep schedule): its first tile (= the tile count: none)
   int32_t tail_cols;     // feature tiles (the last ones, both halves' token tiles) of the split tail
+  int32_t tail_w;        // workgroups the tail's stages are spread over (even; 0: none)
+  int32_t tail_g;        // repeats of the tail's cuts per half
 };
 
 // Buffer descriptor over [base, base + bytes): loads past the end read 0, stores past it are

@@ -1068,7 +1068,7 @@ size_t linear_xent_ws_bytes(int64_t T, int64_t d_out) {
 
 hipError_t launch_linear_xent(const zoact_linear& L, const zoact_arena* A, const void* x, int64_t T, const void* p,
                               const zoact_pert_pair& pert, const int32_t* tokens, int64_t S, float* loss_pm, void* ws,
-                              hipStream_t s) {
+                              size_t ws_bytes, hipStream_t s) {
   GemmArgs a = bf16_args(L, A, x, T, p, nullptr, pert, nullptr);
   const int64_t nblk = (L.d_out + 127) / 128;
   char* w = static_cast<char*>(ws);
@@ -1080,6 +1080,10 @@ hipError_t launch_linear_xent(const zoact_linear& L, const zoact_arena* A, const
   a.tok = tokens;
   a.seq = S;
   a.xnblk = (int32_t)nblk;
+  // what the caller gives beyond the loss's own buffers holds the split tail's partial sums
+  const size_t own = (linear_xent_ws_bytes(T, L.d_out) + 255) / 256 * 256;
+  a.tail_ws = ws_bytes > own ? reinterpret_cast<float*>(static_cast<char*>(ws) + own) : nullptr;
+  a.tail_ws_bytes = ws_bytes > own ? (int64_t)(ws_bytes - own) : 0;
   const hipError_t e = launch_linear_pm_4w64(a, L.w_dtype, EPI_XENT, false, false, s);
   if (e != hipSuccess) return e;
   return launch_xent_combine(a.xpart, a.xtgt, T, S, (int)nblk, T / S, part, loss_pm, s);

@@ -24,6 +24,7 @@
 //    on: a tile's last two stages load the next tile's first two, so the next tile needs
 //    no prologue, and the epilogue works from the accumulators without LDS while those
 //    loads land.
+#include <numeric>
 #include <type_traits>
 
 #include "gemm_4w_epi.hpp"
@@ -55,24 +56,65 @@ __device__ __forceinline__ int dma8_lane_off(int64_t ld) {
 
 __device__ __forceinline__ int mod5(int v) { return v >= 5 ? v - 5 : v; }
 
-// Split tail: with R = ntiles mod grid tiles left for a last, partly idle round (R at most
-// half the grid), those R tiles are each computed as two halves of the depth by two
-// workgroups (virtual tiles tail_first .. tail_first + 2R - 1, tail_first = ntiles - R), so
-// the last round takes half the time.  The R tiles are the last tail_cols feature tiles
-// with every token tile of both halves (R must be a multiple of the token tiles), so a
-// tile and its twin in the other half are computed the same way: the two halves of the
-// ± pair keep identical arithmetic.  A half tile stores its fp32 accumulators (in the
-// accumulator layout, lane-major: coalesced) to tail_ws; a second kernel adds the two
-// halves in the order first + second and runs the same epilogue.
+// Split tail: the R = ntiles mod grid tiles that would make a last, partly idle round (all of
+// them where there are fewer tiles than workgroups) are spread over tail_w workgroups by depth:
+// the stages of the tail's tiles, tile after tile, are one sequence that is cut into equal
+// contiguous shares.  tail_w / 2 workgroups take half 0's tiles and the others the same cuts of
+// half 1's, so a tile and its twin are summed the same way: the two halves of the pair keep
+// identical arithmetic.  (The R tiles are whole feature-tile columns, the last tail_cols, with
+// every token tile of both halves.)  The cuts repeat tail_g = gcd(shares, tiles) times per half,
+// and shares that start at the same depth (one per repeat and half) are dealt to one XCD, their
+// tiles neighbours, so that they share x and W rows in its L2 while they walk the depth together
+// (fc2 at 1024 tokens per half: 425 us of GEMM with the shares dealt in order, 386 so).  R <= tail_w, so a share touches at most
+// two tiles; cuts fall on pairs of stages (a segment of the ring needs two).  A segment that
+// is not a whole tile stores its fp32 accumulators (in the accumulator layout, lane-major:
+// coalesced) to slot (share + tile) of tail_ws, or slot (share) where every tile is a whole
+// number of shares; a second kernel adds a tile's segments in depth order and runs the epilogue.
+// Forms with a split tail: stored outputs or the cross entropy (the regression loss keeps one
+// partial sum per wave of a whole tile).
+constexpr bool epi_tail(int epi, bool shared) { return epi != EPI_MSE && !shared; }
 struct VTile {
-  int tile, k0, nst, kh;   // tile index, first 64-deep stage, stages, depth half (-1: whole)
+  int tile, k0, nst, slot;   // tile index, first 64-deep stage, stages, partial-sum slot (-1: the whole tile)
 };
-__device__ __forceinline__ VTile vtile(const GemmArgs& a, int v, int NS) {
-  if (v < a.tail_first) return VTile{v, 0, NS, -1};
-  const int u = v - a.tail_first, h0 = (NS + 1) >> 1;
-  return (u & 1) ? VTile{a.tail_first + (u >> 1), h0, NS - h0, 1} : VTile{a.tail_first + (u >> 1), 0, h0, 0};
+// tiles per half and two-stage units of the tail; the first unit of share w of a half
+__device__ __forceinline__ int tail_m(const GemmArgs& a) { return a.tail_cols * a.tiles_m_half; }
+__device__ __forceinline__ int tail_cut(const GemmArgs& a, int w, int U) {
+  return (int)((int64_t)w * tail_m(a) * U / (a.tail_w >> 1));
 }
-// fp32 accumulators of half tile u (virtual index - tail_first): [u][wave][i * 8 + j][lane] x float4
+// Slots before the first one of share w, tile t of half h.
+__device__ __forceinline__ int tail_slot_index(const GemmArgs& a, int h, int w, int t) {
+  const int gh = a.tail_w >> 1, m = tail_m(a), step = gh % m != 0;
+  return h * (gh + step * m) + w + step * t;
+}
+// Item i of this workgroup: its whole tiles (blockIdx + i grid below tail_first), then (TAIL)
+// the one or two segments of its share.  False past the last.
+template <bool TAIL>
+__device__ __forceinline__ bool vtile(const GemmArgs& a, int i, int NS, VTile& vt) {
+  const int v = (int)blockIdx.x + i * (int)gridDim.x;
+  if (v < a.tail_first) {
+    vt = VTile{v, 0, NS, -1};
+    return true;
+  }
+  if constexpr (!TAIL) return false;
+  if ((int)blockIdx.x >= a.tail_w) return false;
+  const int U = NS >> 1;
+  int lin = blockIdx.x;
+  if ((a.tail_w & 7) == 0) lin = (lin & 7) * (a.tail_w >> 3) + (lin >> 3);
+  const int half = lin & 1, g2 = 2 * a.tail_g;
+  const int w = ((lin % g2) >> 1) * ((a.tail_w >> 1) / a.tail_g) + lin / g2;   // repeat, then place in it
+  const int nwhole = ((int)a.tail_first - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x;
+  int b = tail_cut(a, w, U);
+  const int e = tail_cut(a, w + 1, U);
+  int t = b / U;
+  if (i > nwhole) b = ++t * U;   // the second segment starts its tile
+  if (i > nwhole + 1 || b >= e) return false;
+  const int u0 = b - t * U, u1 = min(e - t * U, U);
+  const int k0 = 2 * u0, k1 = u1 == U ? NS : 2 * u1;   // (an odd last stage belongs to the last unit)
+  const int m = tail_m(a);
+  vt = VTile{a.tail_first + half * m + t, k0, k1 - k0, u0 == 0 && u1 == U ? -1 : tail_slot_index(a, half, w, t)};
+  return true;
+}
+// fp32 accumulators of slot u: [u][wave][i * 8 + j][lane] x float4
 __device__ __forceinline__ floatx4* tail_slot(const GemmArgs& a, int u, int wave) {
   return reinterpret_cast<floatx4*>(a.tail_ws) + ((int64_t)u * 4 + wave) * 64 * 64;
 }
@@ -86,13 +128,15 @@ struct TileGeom {
 };
 __device__ __forceinline__ TileGeom tile_geom(const GemmArgs& a, int ntiles, int v, bool shared) {
   const int tiles_m = shared ? a.tiles_m_half : 2 * a.tiles_m_half;   // (shared input: one half's tokens)
-  if (v >= a.tail_first) {   // split tail: feature tile columns past tiles_n - tail_cols
-    const int t = v - a.tail_first;
+  if (v >= a.tail_first) {   // split tail: feature tile columns past tiles_n - tail_cols, half 0's tiles first
+    const int m = tail_m(a);
     TileGeom g;
-    g.tm = t % tiles_m;
-    g.tn = a.tiles_n - a.tail_cols + t / tiles_m;
-    g.half = shared ? 0 : g.tm / a.tiles_m_half;
-    g.m0 = (int64_t)(g.tm % a.tiles_m_half) * 256;
+    g.half = v - a.tail_first >= m ? 1 : 0;
+    const int t0 = v - a.tail_first - g.half * m, per = m / a.tail_g;
+    const int t = (t0 % per) * a.tail_g + t0 / per;   // tiles at the same place of their repeat are neighbours
+    g.tm = t % a.tiles_m_half + g.half * a.tiles_m_half;
+    g.tn = a.tiles_n - a.tail_cols + t / a.tiles_m_half;
+    g.m0 = (int64_t)(t % a.tiles_m_half) * 256;
     g.n0 = (int64_t)g.tn * 256;
     return g;
   }
@@ -217,7 +261,7 @@ __device__ __forceinline__ void rank_correction_pre(const GemmArgs& a, const Til
 // fragments, so the next tile starts without a prologue while this one finishes (rank
 // correction, epilogue straight from the accumulators, no LDS).
 template <int EPI, bool OUT_F32, bool SHARED>
-__global__ void __launch_bounds__(NT, 1) gemm_4w64_kernel(GemmArgs a, int ntiles, int nvirt) {
+__global__ void __launch_bounds__(NT, 1) gemm_4w64_kernel(GemmArgs a, int ntiles) {
   constexpr bool PERM = epi_perm(EPI);
   extern __shared__ __align__(16) uint16_t lds[];
   char* const lb = reinterpret_cast<char*>(lds);
@@ -297,8 +341,9 @@ __global__ void __launch_bounds__(NT, 1) gemm_4w64_kernel(GemmArgs a, int ntiles
     }
   };
 
-  int v = blockIdx.x;
-  VTile vt = vtile(a, v, NS);
+  int item = 0;
+  VTile vt;
+  if (!vtile<epi_tail(EPI, SHARED)>(a, 0, NS, vt)) return;   // (uniform: more workgroups than whole tiles and shares)
   TileGeom g = tile_geom(a, ntiles, vt.tile, SHARED);
   __amdgpu_buffer_rsrc_t xrs = buffer_rsrc(a.x + (int64_t)g.half * a.T * a.K, xbytes);
 
@@ -337,7 +382,7 @@ __global__ void __launch_bounds__(NT, 1) gemm_4w64_kernel(GemmArgs a, int ntiles
 #pragma unroll
       for (int j = 0; j < 8; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
     const int p_half = SHARED ? 0 : g.half, c_half = SHARED ? 1 : g.half;
-    const bool corr = a.r > 0 && vt.kh <= 0 && !(g.n0 >= a.plain_begin && g.n0 < a.plain_end);
+    const bool corr = a.r > 0 && vt.k0 == 0 && !(g.n0 >= a.plain_begin && g.n0 < a.plain_end);
     // (the first correction step's operands requested now, see rank_correction_pre)
     const bool pre = EPI == ZOACT_EPI_SWIGLU && corr && (a.r & 7) == 0;
     bf16x8 cpa[8], cpb[8];
@@ -345,9 +390,8 @@ __global__ void __launch_bounds__(NT, 1) gemm_4w64_kernel(GemmArgs a, int ntiles
     // nothing from LDS in flight when the main loop starts (as at the end of each of its
     // iterations), so the compiler places no LDS waits inside it
     __builtin_amdgcn_s_waitcnt(WAIT_LGKM0);
-    const int vn = v + (int)gridDim.x;
-    const bool has_next = vn < nvirt;
-    const VTile vtn = vtile(a, has_next ? vn : v, NS);
+    VTile vtn = vt;
+    const bool has_next = vtile<epi_tail(EPI, SHARED)>(a, item + 1, NS, vtn);
     const TileGeom gn = tile_geom(a, ntiles, vtn.tile, SHARED);
     const __amdgpu_buffer_rsrc_t xrs_n = buffer_rsrc(a.x + (int64_t)gn.half * a.T * a.K, xbytes);
 
@@ -399,9 +443,9 @@ __global__ void __launch_bounds__(NT, 1) gemm_4w64_kernel(GemmArgs a, int ntiles
     // tile inside the plain feature range has none
     if (corr) rank_correction<PERM>(a, acc, fa1, fb1, g, p_half, c_half, wave, lane, pre, cpa, cpb);
 
-    if (vt.kh >= 0) {
-      // half a tile: its accumulators to the split tail's slot, the epilogue runs later
-      floatx4* slot = tail_slot(a, v - a.tail_first, wave);
+    if (epi_tail(EPI, SHARED) && vt.slot >= 0) {
+      // part of a tile: its accumulators to the split tail's slot, the epilogue runs later
+      floatx4* slot = tail_slot(a, vt.slot, wave);
 #pragma unroll
       for (int i = 0; i < 8; ++i)
 #pragma unroll
@@ -415,7 +459,7 @@ __global__ void __launch_bounds__(NT, 1) gemm_4w64_kernel(GemmArgs a, int ntiles
       epilogue_regs<EPI, OUT_F32>(a, acc, tq, wave, lane, g.m0, g.n0, SHARED ? 1 : g.half, g.tm, g.tn);
     }
     if (!has_next) break;
-    v = vn;
+    ++item;
     vt = vtn;
     g = gn;
     xrs = xrs_n;
@@ -424,23 +468,71 @@ __global__ void __launch_bounds__(NT, 1) gemm_4w64_kernel(GemmArgs a, int ntiles
   __builtin_amdgcn_s_waitcnt(WAIT_VM0);
 }
 
-// The split tail's R tiles: workgroup t adds the two halves of tile tail_first + t (first +
-// second, the same order for every run) and runs the tile's epilogue on the sum.
+// Adds the segments of the split tail's tiles (in depth order) and runs the epilogue: workgroup
+// (tile, j) takes the 16-token block j of every wave's 128 x 128 outputs, so that a tail of few
+// tiles, cut into many segments, is still read by many compute units.
 template <int EPI, bool OUT_F32>
-__global__ void __launch_bounds__(NT, 1) tail_combine_kernel(GemmArgs a, int ntiles) {
+__global__ void __launch_bounds__(NT) tail_combine_kernel(GemmArgs a, int ntiles) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
-  const int t = blockIdx.x;
-  const TileGeom g = tile_geom(a, ntiles, a.tail_first + t, false);
-  const floatx4* h0 = tail_slot(a, 2 * t, wave);
-  const floatx4* h1 = tail_slot(a, 2 * t + 1, wave);
-  floatx4 acc[8][8];
+  const int tile = blockIdx.x >> 3, j = blockIdx.x & 7;
+  const int m = tail_m(a), gh = a.tail_w >> 1, U = (int)(a.K >> 6) >> 1;
+  const int half = tile >= m ? 1 : 0, t = tile - half * m;
+  // shares that touch the tile's units [t U, (t + 1) U)
+  const int64_t mu = (int64_t)m * U;
+  int w0 = (int)((int64_t)t * U * gh / mu);
+  while (w0 > 0 && tail_cut(a, w0, U) > t * U) --w0;
+  while (tail_cut(a, w0 + 1, U) <= t * U) ++w0;
+  int w1 = w0;
+  while (tail_cut(a, w1 + 1, U) < (t + 1) * U) ++w1;
+  if (w0 == w1) return;   // one share holds the whole tile and has written its outputs
+  const TileGeom g = tile_geom(a, ntiles, a.tail_first + tile, false);
+  const int64_t tok = g.m0 + (wave >> 1) * 128 + j * 16 + (lane & 15);
+  const int64_t nw = g.n0 + (wave & 1) * 128;
+  floatx4 v[8];
+  const floatx4* sp = tail_slot(a, tail_slot_index(a, half, w0, t), wave) + j * 64 + lane;
 #pragma unroll
-  for (int i = 0; i < 8; ++i)
+  for (int i = 0; i < 8; ++i) v[i] = sp[i * 512];
+#pragma unroll 2
+  for (int w = w0 + 1; w <= w1; ++w) {
+    sp += 4 * 64 * 64;   // (a tile's slots lie together)
 #pragma unroll
-    for (int j = 0; j < 8; ++j) acc[i][j] = h0[(i * 8 + j) * 64 + lane] + h1[(i * 8 + j) * 64 + lane];
-  uint4 tq[8][4];
-  epilogue_regs<EPI, OUT_F32>(a, acc, tq, wave, lane, g.m0, g.n0, g.half, g.tm, g.tn);
+    for (int i = 0; i < 8; ++i) v[i] += sp[i * 512];
+  }
+  if constexpr (EPI == EPI_XENT) emit_xent(a, v, half, tok, nw, lane);
+  else emit<EPI, OUT_F32, 8>(a, v, half, tok, nw, lane >> 4);
+}
+
+// The split tail's workgroups (w, 0: none) and feature-tile columns, for tiles_mh token tiles per
+// half and tiles_n feature tiles on ncu compute units.
+//
+// A partial sum's way out and back is about 0.1 us per 256 KB slot over the chip (measured 160
+// slots: 17 us, 416: 28 us in the second launch, the stores 6 to 12 more) against 1.35 us per
+// stage, so w = sqrt(R NS 1.35 / 0.09) workgroups balance the two, at most one per compute unit
+// and at least one per tile.  Split only where that leaves 8% of the launch, and up to 0.65 tiles
+// per compute unit: the clock falls as the chip fills (fc2: 1.5 us a stage with 160 busy compute
+// units, 1.9 with all), so 200 and 240 tiles ran 557 and 583 us split, 478 and 542 whole; 160
+// tiles 430 split, 524 whole.
+struct TailPlan {
+  int w, cols;
+};
+TailPlan plan_tail(int tiles_mh, int tiles_n, int NS, int64_t ws_bytes, int ncu) {
+  const int tiles_m = 2 * tiles_mh, ntiles = tiles_m * tiles_n, grid = ncu & ~1;
+  const int R = ntiles % ncu;
+  if (R == 0 || 100 * R > 65 * ncu || (ncu & 1) || R % tiles_m != 0 || NS < 8) return {0, 0};
+  const int64_t slots = ws_bytes / (256 * 1024);
+  int w = (int)__builtin_sqrt(15.0 * R * NS);
+  w = w > grid ? grid : w;
+  w = (w + R - 1) / R * R > grid ? w : (w + R - 1) / R * R;   // whole shares per tile where they fit
+  if (w < R) w = R;
+  if (w % R != 0 ? w + R > slots : w > slots) w = (int)slots - R;
+  w &= ~1;
+  const int u2 = R * (NS >> 1);                               // no more shares than units
+  if (w > u2) w = u2 & ~1;
+  if (w <= R) return {0, 0};
+  const double rounds = ntiles / ncu, c = 1.35;
+  const double whole = (rounds + 1) * NS * c, split = (rounds * NS + (double)R * NS / w) * c + 0.09 * (w % R ? w + R : w) + 4.0;
+  return split < 0.92 * whole ? TailPlan{w, R / tiles_m} : TailPlan{0, 0};
 }
 
 // ---------------------------------------------------------------------------------------
@@ -746,7 +838,8 @@ hipError_t launch_i4w64(const GemmArgs& a_in, hipStream_t s) {
   if (ncu <= 0) return hipErrorInvalidDevice;
   const unsigned grid = (unsigned)(ntiles < ncu ? ntiles : ncu);
   a.tail_first = ntiles;
-  a.tail_cols = 0;
+  a.tail_cols = a.tail_w = 0;
+  a.tail_g = 1;
   gemm_i4w64_kernel<EPI, OUT_F32><<<dim3(grid), dim3(NT), I4_LDS_BYTES, s>>>(a, ntiles);
   return hipGetLastError();
 }
@@ -764,20 +857,20 @@ hipError_t launch_4w64(const GemmArgs& a_in, hipStream_t s) {
   const int ntiles = (SHARED ? 1 : 2) * a.tiles_m_half * a.tiles_n;
   const int ncu = cu_count();
   if (ncu <= 0) return hipErrorInvalidDevice;
-  const unsigned grid = (unsigned)(ntiles < ncu ? ntiles : ncu);
-  // the split tail where it applies: plain or ReLU outputs, a last round at most half
-  // full after at least one full one and made of whole feature-tile columns, at least 4
-  // stages (2 per half), a workspace
-  const int rest = ntiles % (int)grid, tiles_m = 2 * a.tiles_m_half;
-  const bool split = (EPI == 0 || EPI == ZOACT_EPI_RELU) && !SHARED && ntiles > (int)grid && rest > 0 &&
-                     2 * rest <= (int)grid && rest % tiles_m == 0 && (a.K >> 6) >= 4 && a.tail_ws != nullptr &&
-                     a.tail_ws_bytes >= (int64_t)rest * 2 * 4 * 64 * 64 * 16;
-  a.tail_first = split ? ntiles - rest : ntiles;
-  a.tail_cols = split ? rest / tiles_m : 0;
-  const int nvirt = split ? ntiles + rest : ntiles;
-  gemm_4w64_kernel<EPI, OUT_F32, SHARED><<<dim3(grid), dim3(NT), LDS_BYTES, s>>>(a, ntiles, nvirt);
-  if constexpr ((EPI == 0 || EPI == ZOACT_EPI_RELU) && !SHARED) {
-    if (split) tail_combine_kernel<EPI, OUT_F32><<<dim3((unsigned)rest), dim3(NT), 0, s>>>(a, ntiles);
+  // the split tail where it applies and there is a workspace for it
+  constexpr bool TAIL = epi_tail(EPI, SHARED);
+  TailPlan tp{0, 0};
+  if (TAIL && a.tail_ws != nullptr) tp = plan_tail(a.tiles_m_half, a.tiles_n, (int)(a.K >> 6), a.tail_ws_bytes, ncu);
+  a.tail_w = tp.w;
+  a.tail_cols = tp.cols;
+  a.tail_g = tp.w ? std::gcd(tp.w / 2, tp.cols * a.tiles_m_half) : 1;
+  a.tail_first = ntiles - tp.cols * 2 * a.tiles_m_half;
+  const int want = a.tail_first > tp.w ? a.tail_first : tp.w;
+  const unsigned grid = (unsigned)(want < ncu ? want : ncu);
+  gemm_4w64_kernel<EPI, OUT_F32, SHARED><<<dim3(grid), dim3(NT), LDS_BYTES, s>>>(a, ntiles);
+  if constexpr (TAIL) {
+    if (tp.w > 0)
+      tail_combine_kernel<EPI, OUT_F32><<<dim3((unsigned)((ntiles - a.tail_first) * 8)), dim3(NT), 0, s>>>(a, ntiles);
   }
   return hipGetLastError();
 }
@@ -798,6 +891,15 @@ int cu_count() {
   return cache[dev];
 }
 
+
+// Workspace the split tail of T tokens per half and d_out features can use: a slot per
+// workgroup and one per tile of the last round.
+size_t tail_ws_bytes(int64_t T, int64_t d_out) {
+  const int64_t ncu = cu_count();
+  if (ncu <= 0) return 0;
+  const int64_t rest = 2 * ((T + 255) / 256) * ((d_out + 255) / 256) % ncu;
+  return rest ? (size_t)(ncu + rest) * 256 * 1024 : 0;
+}
 
 // Returns hipErrorNotSupported outside this schedule's coverage: bf16 weights; C_h
 // precomputed (or r = 0), r <= 256; depth a multiple of 64, at least 128; a half of x,

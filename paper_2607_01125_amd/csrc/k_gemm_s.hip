@@ -25,6 +25,7 @@
 //   o 4096 -> 4096        14 / 16 / 28 / 64     was 75 / 74 / 78 / 82
 //   down 14336 -> 4096    30 / 41 / 76 / 223    was 243 / 245 / 295 / 290
 //   fc2 20480 -> 5120     48 / 64 / 121 / 511   was 413 / 422 / 581 / 551
+#include <algorithm>
 #include <type_traits>
 
 #include "gemm_4w_epi.hpp"
@@ -89,71 +90,6 @@ __device__ __forceinline__ floatx4* part_slot(const GemmArgs& a, const SPlan& pl
   const int per = SHARED ? pl.nslice + 1 : pl.nslice;
   const int idx = SHARED ? (slice == 0 ? half : slice + 1) : slice;
   return reinterpret_cast<floatx4*>(a.tail_ws) + (((int64_t)tile * per + idx) * 4 + wave) * (NB * 2) * 64;
-}
-
-// The epilogue of one token block of a wave: NI 16-feature blocks of accumulators, token
-// (half, t), first feature nw.  The operations and their order are those of the 256 x 256
-// schedule's register epilogue.
-template <int EPI, bool OUT_F32, int NI>
-__device__ __forceinline__ void emit(const GemmArgs& a, const floatx4 (&v)[NI], int half, int64_t t, int64_t nw,
-                                     int lk) {
-  if (t >= a.T) return;
-  const int64_t row = (int64_t)half * a.T + t;
-  if constexpr (EPI == ZOACT_EPI_SWIGLU) {
-    const int64_t nout = a.N / 2;
-#pragma unroll
-    for (int q = 0; q < NI / 2; ++q) {
-      const int64_t ng = nw + q * 32 + lk * 4, no = nw / 2 + q * 16 + lk * 4;
-      if (nw + q * 32 >= a.N) continue;
-      float g[4], u[4], o[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) g[e] = v[2 * q][e], u[e] = v[2 * q + 1][e];
-      if (a.bias) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) g[e] += bf2f(a.bias[ng + e]), u[e] += bf2f(a.bias[ng + 16 + e]);
-      }
-#pragma unroll
-      for (int e = 0; e < 4; ++e) o[e] = silu(g[e]) * u[e];
-      if (a.resid) {
-        const uint2 rv = *reinterpret_cast<const uint2*>(a.resid + row * nout + no);
-        o[0] += bf_lo(rv.x), o[1] += bf_hi(rv.x), o[2] += bf_lo(rv.y), o[3] += bf_hi(rv.y);
-      }
-      *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.y) + row * nout + no) =
-          make_uint2(pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3]));
-    }
-  } else {
-#pragma unroll
-    for (int q = 0; q < NI / 2; ++q) {
-      const int64_t n = nw + q * 32 + lk * 8;
-      if (n >= a.N) continue;
-      float o[8];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) o[e] = v[2 * q][e], o[4 + e] = v[2 * q + 1][e];
-      if (a.bias) {   // (its alignment is not part of the contract)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) o[e] += bf2f(a.bias[n + e]);
-      }
-      if (a.resid) {
-        const uint4 rv = *reinterpret_cast<const uint4*>(a.resid + row * a.N + n);
-        const uint32_t w[4] = {rv.x, rv.y, rv.z, rv.w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) o[2 * e] += bf_lo(w[e]), o[2 * e + 1] += bf_hi(w[e]);
-      }
-      if (EPI == ZOACT_EPI_RELU) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) o[e] = fmaxf(o[e], 0.0f);
-      }
-      if (OUT_F32) {
-        float* yp = reinterpret_cast<float*>(a.y) + row * a.N + n;
-        *reinterpret_cast<float4*>(yp) = make_float4(o[0], o[1], o[2], o[3]);
-        *reinterpret_cast<float4*>(yp + 4) = make_float4(o[4], o[5], o[6], o[7]);
-      } else {
-        *reinterpret_cast<uint4*>(reinterpret_cast<uint16_t*>(a.y) + row * a.N + n) =
-            make_uint4(pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3]), pack_bf16x2(o[4], o[5]),
-                       pack_bf16x2(o[6], o[7]));
-      }
-    }
-  }
 }
 
 // Rank-r correction of half h added to the blocks j with half_j[j] == h (all of them with a
@@ -563,7 +499,9 @@ hipError_t launch_linear_pm_s(const GemmArgs& a, int w_dtype, int epi, bool out_
     return hipErrorNotSupported;
   const int ncu = cu_count();
   if (ncu <= 0) return hipErrorInvalidDevice;
-  const Choice c = choose(a.T, a.N, a.K, a.tail_ws ? a.tail_ws_bytes : 0, ncu);
+  // (the sweep the cost is fitted to had 256 KB per compute unit)
+  const int64_t wsb = a.tail_ws ? std::min<int64_t>(a.tail_ws_bytes, (int64_t)ncu * 256 * 1024) : 0;
+  const Choice c = choose(a.T, a.N, a.K, wsb, ncu);
   if (c.nb == 0) return hipErrorNotSupported;
   SPlan pl{};
   pl.nbt = (int32_t)((a.T + 15) / 16);
