@@ -724,6 +724,25 @@ void cross(const double* a, const double* bm, int64_t d, int b, double* mp, doub
   reduce_parts_kernel<<<(unsigned)(((int64_t)b * b + 63) / 64), 256, 0, s>>>(mp, np, (int64_t)b * b, m);
 }
 
+// 1 / sqrt(x) and 1 / x for normal x, from the hardware's approximation (relative error near
+// 2^-24 or better) and two Newton steps with the residual formed exactly: within a few units of
+// the last place.
+__device__ __forceinline__ double rsqrt_nr(double x) {
+  double y = __builtin_amdgcn_rsq(x);
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const double h = 0.5 * y, g = x * y;
+    y = fma(h, fma(-g, y, 1.0), y);
+  }
+  return y;
+}
+__device__ __forceinline__ double rcp_nr(double x) {
+  double y = __builtin_amdgcn_rcp(x);
+#pragma unroll
+  for (int k = 0; k < 2; ++k) y = fma(y, fma(-x, y, 1.0), y);
+  return y;
+}
+
 // M = L L^T (left-looking Cholesky), then X = L^{-1} by forward substitution, written
 // out transposed: linvt[k][j] = X[j][k].  For blocks past the register-blocked kernel
 // below (b > 128): one workgroup, one lane per row (or column), the matrix in `scratch`
@@ -836,7 +855,7 @@ __global__ void __launch_bounds__(1024) chol_inv_blk_kernel(const double* __rest
     }
     __syncthreads();
     const double pv = cj[j] > 1e-300 ? cj[j] : 1e-300;
-    const double ipv = 1.0 / pv;
+    const double ipv = rcp_nr(pv);
     if (k0 + BS - 1 > j && i0 + BS - 1 > j) {   // block reaches past row and column j
       double ck[BS];
 #pragma unroll
@@ -912,12 +931,14 @@ __global__ void __launch_bounds__(1024) chol_inv_blk_kernel(const double* __rest
 }
 
 // q[i][j] = sum over k <= j of y[i][k] linvt[k][j]  (Q = Y L^{-T}); also the fp32 copy.
-// Rows are processed 256 / b at a time (b <= 256: one thread per output), staged in LDS.
+// Rows are processed 256 / b at a time (b <= 256: one thread per output), staged in LDS beside
+// L^{-T} where b <= LB: with LB = 64 (33 KB) four workgroups share a CU, with 128 one does.
+template <int LB>
 __global__ void __launch_bounds__(256) apply_linv_kernel(const double* __restrict__ y, const double* __restrict__ linvt,
                                                          int64_t d, int b, double* __restrict__ q, float* __restrict__ q32) {
-  __shared__ double lt[128 * 128];
+  __shared__ double lt[LB * LB];
   __shared__ double yr[256];
-  const bool in_lds = b <= 128;
+  const bool in_lds = b <= LB;
   if (in_lds) {
     for (int e = threadIdx.x; e < b * b; e += 256) lt[e] = linvt[e];
   }
@@ -1110,8 +1131,26 @@ __global__ void __launch_bounds__(256) jacobi_kernel(const double* __restrict__ 
 // column (stride BP + 1); each pair is worked on by 16 lanes, BP / 16 rows each, held in
 // registers between the pair's dot products and its update (8 BP threads: several waves
 // per SIMD hide each other's latency); one barrier per round.  A pair rotates when
-// |a_p . a_q| > 1e-15 ||a_p|| ||a_q||; the sweeps stop once the largest such ratio of a
-// sweep is at most 1e-13.  Outputs as jacobi_kernel.
+// |a_p . a_q| > 1e-15 ||a_p|| ||a_q||; the sweeps stop once the largest such ratio a sweep met
+// is at most 1e-9: they converge quadratically, so what is left after that sweep is below
+// rounding (1e-13 spent one more sweep, of seven, on the same result).
+//
+// One workgroup, so a round's serial chain bounds it: the dot products' sums over the 16 lanes
+// run in the vector unit (row rotations) and the rotation is three reciprocal (square root)
+// approximations with Newton steps instead of three divisions and three square roots:
+// 519 us a solve at b = 64 before, 313 so.  Outputs as jacobi_kernel.
+
+// Sum over the 16 lanes of a row, the same bits in each.
+template <int ROR>
+__device__ __forceinline__ double row_ror_add(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, 0x120 + ROR, 0xF, 0xF, false);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), 0x120 + ROR, 0xF, 0xF, false);
+  return v + __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ double row_sum(double v) {
+  return row_ror_add<1>(row_ror_add<2>(row_ror_add<4>(row_ror_add<8>(v))));
+}
 template <int BP>
 __global__ void __launch_bounds__(8 * BP) jacobi1s_kernel(const double* __restrict__ hg, double* __restrict__ s_out,
                                                           double* __restrict__ theta, int* __restrict__ order, int b,
@@ -1160,19 +1199,19 @@ __global__ void __launch_bounds__(8 * BP) jacobi1s_kernel(const double* __restri
             be1 = fma(aq[k + 1], aq[k + 1], be1);
             ga1 = fma(ap[k + 1], aq[k + 1], ga1);
           }
-          double al = al0 + al1, be = be0 + be1, ga = ga0 + ga1;
-#pragma unroll
-          for (int o = 1; o < G; o <<= 1) {
-            al += __shfl_xor(al, o, 64);
-            be += __shfl_xor(be, o, 64);
-            ga += __shfl_xor(ga, o, 64);
-          }
-          const double nn = sqrt(al * be);
-          if (fabs(ga) > 1e-15 * nn && fabs(ga) > 1e-300) {
-            worst = fmax(worst, fabs(ga) / nn);
-            const double zeta = (be - al) / (2.0 * ga);
-            const double tq = (zeta >= 0 ? 1.0 : -1.0) / (fabs(zeta) + sqrt(1.0 + zeta * zeta));
-            const double cc = 1.0 / sqrt(1.0 + tq * tq), ss = tq * cc;
+          const double al = row_sum(al0 + al1), be = row_sum(be0 + be1), ga = row_sum(ga0 + ga1);
+          const double ab = al * be, gg = ga * ga;
+          if (gg > 1e-30 * ab && fabs(ga) > 1e-300) {
+            worst = fmax(worst, gg * __builtin_amdgcn_rcp(ab));   // (the ratio's square)
+            // tan(2 phi) = 2 ga / (be - al), the smaller angle: t = 2 ga / (d +- sqrt(d^2 + 4 ga^2)).
+            // Only t's ratio matters, so the pair's scale is taken out first (no overflow of squares).
+            const int ex = -__builtin_amdgcn_frexp_exp(fmax(al, be));
+            const double d = ldexp(be - al, ex), g2 = ldexp(2.0 * ga, ex);
+            const double h2 = fma(d, d, g2 * g2);
+            const double h = h2 > 1e-280 ? h2 * rsqrt_nr(h2) : 0.0;
+            const double den = fabs(d) + h;
+            const double tq = den > 1e-140 ? (d >= 0 ? g2 : -g2) * rcp_nr(den) : (ga >= 0 ? 1.0 : -1.0);
+            const double cc = rsqrt_nr(fma(tq, tq, 1.0)), ss = tq * cc;
 #pragma unroll
             for (int k = 0; k < RPL; ++k) {
               A[p * LD + k * G + gl] = cc * ap[k] - ss * aq[k];
@@ -1191,7 +1230,7 @@ __global__ void __launch_bounds__(8 * BP) jacobi1s_kernel(const double* __restri
 #pragma unroll
     for (int q = 0; q < NW; ++q) w = fmax(w, wmax[q]);
     __syncthreads();
-    if (w <= 1e-13) break;
+    if (w <= 1e-18) break;   // (squares: a ratio of 1e-9)
   }
   if (t < b) {
     double s2 = 0.0;
@@ -1395,13 +1434,16 @@ void chol_inv(EigWs& w, int b, hipStream_t s) {
 // iteration one pass keeps the block well conditioned; the block handed to
 // Rayleigh-Ritz gets two, which makes it orthonormal to working precision.
 hipError_t orth(EigWs& w, int64_t d, int b, int passes, hipStream_t s) {
-  const unsigned gapp = (unsigned)((d * b + 255) / 256 > 256 ? 256 : (d * b + 255) / 256);
+  const int64_t gmax = b <= 64 ? 1024 : 256, gneed = (d * b + 255) / 256;
+  const unsigned gapp = (unsigned)(gneed > gmax ? gmax : gneed);
   double* src = w.y;
   double* dst = w.q;
   for (int pass = 0; pass < passes; ++pass) {
     cross(src, src, d, b, w.mp, w.m, s);
     chol_inv(w, b, s);
-    apply_linv_kernel<<<gapp, 256, 0, s>>>(src, w.linvt, d, b, dst, pass == passes - 1 ? w.q32 : nullptr);
+    float* q32 = pass == passes - 1 ? w.q32 : nullptr;
+    if (b <= 64) apply_linv_kernel<64><<<gapp, 256, 0, s>>>(src, w.linvt, d, b, dst, q32);
+    else apply_linv_kernel<128><<<gapp, 256, 0, s>>>(src, w.linvt, d, b, dst, q32);
     double* t = src;
     src = dst;
     dst = t;
