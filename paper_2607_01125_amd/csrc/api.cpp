@@ -500,10 +500,15 @@ zoact_status zoact_basis_init(const void* x, int32_t x_dtype, int64_t n_tok, int
     return ZOACT_OK;
   }
   float* g = static_cast<float*>(ws);
-  zoact_status s = zoact_gram(x, x_dtype, n_tok, d, ld_x, g, 0, stream);
+  char* const sws = static_cast<char*>(ws) + gbytes;
+  // the Gram through X^T (in the solver's part of ws, not in use yet) and the GEMM where it fits
+  hipError_t e = hipErrorNotSupported;
+  if (x && x_dtype == ZOACT_BF16 && ld_x >= d && ld_x % 8 == 0 && aligned16(x) && aligned16(ws))
+    e = zoact::launch_gram_t(static_cast<const uint16_t*>(x), n_tok, d, ld_x, g, sws, ws_bytes - gbytes, st(stream));
+  zoact_status s = e == hipErrorNotSupported ? zoact_gram(x, x_dtype, n_tok, d, ld_x, g, 0, stream)
+                                             : hip_status(e, "basis_init");
   if (s != ZOACT_OK) return s;
-  return zoact_basis_from_gram(g, d, r, opts, ut, ut_dtype, ut_master, eigvals, report,
-                               static_cast<char*>(ws) + gbytes, ws_bytes - gbytes, stream);
+  return zoact_basis_from_gram(g, d, r, opts, ut, ut_dtype, ut_master, eigvals, report, sws, ws_bytes - gbytes, stream);
 }
 
 }  // extern "C"

@@ -50,7 +50,7 @@ hipError_t launch_linear_pm(const zoact_linear& L, const zoact_arena* A, const v
 // stored): per-tile sums into part [2][tiles], then loss_pm[h] = sum / (T * d_out).
 // y [2 T][N] fp32 = x [2 T][K] w^T, bf16 operands with dense rows (plain GEMM, no correction).
 hipError_t launch_gemm_nt_f32(const uint16_t* x, int64_t T, const uint16_t* w, int64_t N, int64_t K, float* y,
-                              hipStream_t s);
+                              void* ws, size_t ws_bytes, hipStream_t s);
 hipError_t launch_linear_mse(const zoact_linear& L, const zoact_arena* A, const void* x, int64_t T, uint32_t flags, const void* p,
                              const zoact_pert_pair& pert, const void* target, double* part, float* loss_pm,
                              hipStream_t s);
@@ -78,6 +78,8 @@ hipError_t launch_gram(const void* x, int32_t dtype, int64_t n_tok, int64_t d, i
 hipError_t launch_basis_from_gram(const float* g, int64_t d, int32_t r, int32_t p, const zoact_eig_opts& o, void* ut,
                                   int32_t ut_dtype, float* ut_master, float* eigvals, zoact_eig_report* report, void* ws,
                                   hipStream_t s, bool& met);
+hipError_t launch_gram_t(const uint16_t* x, int64_t n, int64_t d, int64_t ld, float* g, void* xt_ws, size_t bytes,
+                         hipStream_t s);
 size_t basis_ws_bytes(int64_t d, int32_t r, int32_t p);
 // Algorithm 1 from the token-side Gram X X^T of bf16 X [n][ld] (D values per row,
 // D % 64 == 0, r + p <= n): same outputs as the Gram form; ws of basis_rows_ws_bytes.

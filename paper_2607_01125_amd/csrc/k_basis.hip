@@ -67,6 +67,32 @@ __device__ __forceinline__ void transpose8x8(const uint4 (&in)[8], uint4 (&out)[
   }
 }
 
+// xt [d][np] = X^T for bf16 X [n][ld], zeros past n (np >= n and d multiples of 8): 128 x 128 tiles,
+// 8 x 8 blocks transposed in registers and whole 256-byte rows of xt written through LDS.
+__global__ void __launch_bounds__(256) transpose_bf16_kernel(const uint16_t* __restrict__ x, int64_t n, int64_t d,
+                                                             int64_t ld, int64_t np, uint16_t* __restrict__ xt) {
+  constexpr int LDT = 128 + 8;
+  __shared__ __align__(16) uint16_t sm[128 * LDT];   // [feature][token]
+  const int64_t t0 = (int64_t)blockIdx.x * 128, f0 = (int64_t)blockIdx.y * 128;
+  const int hi = threadIdx.x >> 4, lo = threadIdx.x & 15;
+  uint4 rows[8], cols[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const int64_t t = t0 + hi * 8 + e, f = f0 + lo * 8;
+    rows[e] = t < n && f < d ? *reinterpret_cast<const uint4*>(x + t * ld + f) : make_uint4(0u, 0u, 0u, 0u);
+  }
+  transpose8x8(rows, cols);
+#pragma unroll
+  for (int j = 0; j < 8; ++j) *reinterpret_cast<uint4*>(sm + (lo * 8 + j) * LDT + hi * 8) = cols[j];
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const int f = e * 16 + hi;
+    if (f0 + f < d && t0 + lo * 8 < np)
+      *reinterpret_cast<uint4*>(xt + (f0 + f) * np + t0 + lo * 8) = *reinterpret_cast<const uint4*>(sm + f * LDT + lo * 8);
+  }
+}
+
 __global__ void __launch_bounds__(256) gram_bf16_kernel(const uint16_t* __restrict__ x, int64_t n_tok, int64_t d,
                                                         int64_t ld, float* __restrict__ g, int accumulate, int ntile) {
   // upper-triangular tile index -> (ti, tj), ti <= tj
@@ -1490,6 +1516,34 @@ hipError_t launch_gram(const void* x, int32_t dtype, int64_t n_tok, int64_t d, i
   return hipGetLastError();
 }
 
+// Both triangles of g [n][n] from its upper one, so the matrix is exactly symmetric.
+static void mirror(float* g, int64_t n, hipStream_t s) {
+  const int nt = (int)((n + 31) / 32);
+  if (nt > 1) mirror_upper_kernel<<<dim3((unsigned)((int64_t)nt * (nt - 1) / 2)), 256, 0, s>>>(g, n, nt);
+  mirror_diag_kernel<<<dim3((unsigned)nt), 256, 0, s>>>(g, n);
+}
+
+// G = X^T X through X^T and the plain bf16 GEMM (both halves of X^T's rows against all of them),
+// mirrored; xt_ws holds X^T (its rows padded with zeros to the GEMM's 64-deep stages) and, past it,
+// the GEMM's partial sums.  The triangle kernel
+// walks all tokens in each of its 128 x 128 tiles, 137 us at 4096 tokens however few tiles there
+// are, and 528 tiles (d = 4096) exceed two per compute unit: 275 us.  So 142 us there (transpose 12, GEMM 104,
+// mirror 25).
+// hipErrorNotSupported where the GEMM's 64-deep schedules do not cover the shape.
+hipError_t launch_gram_t(const uint16_t* x, int64_t n, int64_t d, int64_t ld, float* g, void* xt_ws, size_t bytes,
+                         hipStream_t s) {
+  const int64_t np = n <= 128 ? 128 : (n + 63) / 64 * 64;
+  const size_t own = align256((size_t)np * d * 2);
+  if (n < 1 || d % 64 != 0 || bytes < own || own >= (size_t(1) << 31) || np > 65535 * 128)
+    return hipErrorNotSupported;
+  uint16_t* xt = static_cast<uint16_t*>(xt_ws);
+  transpose_bf16_kernel<<<dim3((unsigned)((np + 127) / 128), (unsigned)((d + 127) / 128)), 256, 0, s>>>(x, n, d, ld, np, xt);
+  const hipError_t e = launch_gemm_nt_f32(xt, d / 2, xt, d, np, g, static_cast<char*>(xt_ws) + own, bytes - own, s);
+  if (e != hipSuccess) return e;
+  mirror(g, d, s);
+  return hipGetLastError();
+}
+
 // The token-side form: X (bf16 [n][ld], D values per row) whose Gram X X^T the solver
 // ran on, and the buffers that carry its Ritz vectors back to the D features.
 struct Rows {
@@ -1702,11 +1756,9 @@ hipError_t launch_basis_init_rows(const uint16_t* x, int64_t n, int64_t D, int64
   pw += align256((size_t)r * 8);
   rows.part = reinterpret_cast<double*>(pw);
   if (n % 32 == 0 && ld == D) {
-    hipError_t e = launch_gemm_nt_f32(x, n / 2, x, n, D, g, s);
+    hipError_t e = launch_gemm_nt_f32(x, n / 2, x, n, D, g, nullptr, 0, s);
     if (e != hipSuccess) return e;
-    const int nt = (int)((n + 31) / 32);
-    if (nt > 1) mirror_upper_kernel<<<dim3((unsigned)((int64_t)nt * (nt - 1) / 2)), 256, 0, s>>>(g, n, nt);
-    mirror_diag_kernel<<<dim3((unsigned)nt), 256, 0, s>>>(g, n);
+    mirror(g, n, s);
   } else {
     const int nt = (int)((n + GT - 1) / GT);
     gram_rows_bf16_kernel<<<dim3((unsigned)(nt * (nt + 1) / 2)), 256, 0, s>>>(x, n, D, ld, g, nt);
