@@ -412,7 +412,10 @@ __global__ void gram_f32_kernel(const float* __restrict__ x, int64_t n_tok, int6
 // with fp64 accumulation, so the result carries the accuracy of the fp32 Gram.
 constexpr int GQ_ROWS = 128;   // rows of G per workgroup of the products
 constexpr int GQ_K = 32;       // contraction chunk staged in LDS
-constexpr int NPART = 64;      // workgroups (partial sums) of the column-Gram pass
+// Workgroups (partial sums) of the column-Gram pass: a 64-column block's pass is a chain of 32-row
+// chunks on few compute units (13.5 us with 64,
+// 8.5 so at d = 4096), a wider one fills them by its column blocks.
+constexpr int npart(int b) { return b <= 64 ? 128 : 64; }
 
 size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
 
@@ -451,7 +454,7 @@ struct EigWs {
   double* part;   // [ks][d][b] partial products (fp32 or fp64 elements)
   int ks;         // the products' K split (ksplit_for) and its chunk
   int64_t kchunk;
-  double* mp;     // [NPART][b][b] partial column Grams
+  double* mp;     // [npart(b)][b][b] partial column Grams
   double* m;      // [b][b]
   double* linvt;  // [b][b] (L^{-1})^T
   double* chol;   // [b][b + 1] Cholesky / Jacobi work matrix (when it does not fit in LDS)
@@ -472,7 +475,7 @@ EigWs carve(void* ws, int64_t d, int b, int r, int ks) {
   w.y = reinterpret_cast<double*>(p); p += align256((size_t)d * b * 8);
   w.q32 = reinterpret_cast<float*>(p); p += align256((size_t)d * b * 4);
   w.part = reinterpret_cast<double*>(p); p += align256((size_t)ks * d * b * 8);
-  w.mp = reinterpret_cast<double*>(p); p += align256((size_t)NPART * b * b * 8);
+  w.mp = reinterpret_cast<double*>(p); p += align256((size_t)npart(b) * b * b * 8);
   w.m = reinterpret_cast<double*>(p); p += align256((size_t)b * b * 8);
   w.linvt = reinterpret_cast<double*>(p); p += align256((size_t)b * b * 8);
   w.chol = reinterpret_cast<double*>(p); p += align256((size_t)b * (b + 1) * 8);
@@ -489,7 +492,7 @@ EigWs carve(void* ws, int64_t d, int b, int r, int ks) {
 
 size_t carve_bytes(int64_t d, int b, int r, int ks) {
   return align256((size_t)d * b * 8) * 2 + align256((size_t)d * b * 4) + align256((size_t)ks * d * b * 8) +
-         align256((size_t)NPART * b * b * 8) + align256((size_t)b * b * 8) * 3 + align256((size_t)b * (b + 1) * 8) * 2 +
+         align256((size_t)npart(b) * b * b * 8) + align256((size_t)b * b * 8) * 3 + align256((size_t)b * (b + 1) * 8) * 2 +
          align256((size_t)b * 8) +
          align256((size_t)b * 4) + align256((size_t)d * r * 8) + align256((size_t)b * b * 8) + 512;
 }
@@ -721,25 +724,32 @@ __global__ void __launch_bounds__(256) cross_partial_kernel(const double* __rest
 }
 
 // m[e] = sum over p of mp[p][e] in a fixed order: 64 entries per workgroup, each summed
-// by 4 threads over interleaved quarters of the partials, then the 4 sums in order.
-__global__ void __launch_bounds__(256) reduce_parts_kernel(const double* __restrict__ mp, int np, int64_t n,
-                                                           double* __restrict__ m) {
-  __shared__ double sh[4][64];
-  const int64_t e = (int64_t)blockIdx.x * 64 + (threadIdx.x & 63);
-  const int q = threadIdx.x >> 6;
+// by 16 threads over interleaved sixteenths of the partials, then the 16 sums in order.
+__global__ void __launch_bounds__(1024) reduce_parts_kernel(const double* __restrict__ mp, int np, int64_t n,
+                                                            double* __restrict__ m) {
+  __shared__ double sh[16][64];
+  const int l = threadIdx.x & 63, q = threadIdx.x >> 6;
+  const int64_t e = (int64_t)blockIdx.x * 64 + l;
   double s = 0.0;
-  if (e < n)
-    for (int p = q; p < np; p += 4) s += mp[(int64_t)p * n + e];
-  sh[q][threadIdx.x & 63] = s;
+  if (e < n) {
+#pragma unroll 4
+    for (int p = q; p < np; p += 16) s += mp[(int64_t)p * n + e];
+  }
+  sh[q][l] = s;
   __syncthreads();
-  if (q == 0 && e < n) m[e] = ((sh[0][threadIdx.x] + sh[1][threadIdx.x]) + sh[2][threadIdx.x]) + sh[3][threadIdx.x];
+  if (q == 0 && e < n) {
+    double t = sh[0][l];
+#pragma unroll
+    for (int k = 1; k < 16; ++k) t += sh[k][l];
+    m[e] = t;
+  }
 }
 
 // M = A^T B for A, B [d][b] (fp64), deterministic: partial sums over row chunks, then
 // their sum in partial order.
 void cross(const double* a, const double* bm, int64_t d, int b, double* mp, double* m, hipStream_t s) {
-  int np = (int)((d + 63) / 64);
-  np = np < 1 ? 1 : (np > NPART ? NPART : np);
+  int np = (int)((d + 31) / 32);
+  np = np > npart(b) ? npart(b) : np;
   if (b <= 64) {
     const int nbk = (b + 63) / 64;
     cross_partial_kernel<4><<<dim3((unsigned)np, (unsigned)(nbk * nbk)), 256, 0, s>>>(a, bm, d, b, mp);
@@ -747,7 +757,7 @@ void cross(const double* a, const double* bm, int64_t d, int b, double* mp, doub
     const int nbk = (b + 127) / 128;
     cross_partial_kernel<8><<<dim3((unsigned)np, (unsigned)(nbk * nbk)), 256, 0, s>>>(a, bm, d, b, mp);
   }
-  reduce_parts_kernel<<<(unsigned)(((int64_t)b * b + 63) / 64), 256, 0, s>>>(mp, np, (int64_t)b * b, m);
+  reduce_parts_kernel<<<(unsigned)(((int64_t)b * b + 63) / 64), 1024, 0, s>>>(mp, np, (int64_t)b * b, m);
 }
 
 // 1 / sqrt(x) and 1 / x for normal x, from the hardware's approximation (relative error near
