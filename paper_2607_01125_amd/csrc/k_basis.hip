@@ -413,8 +413,8 @@ __global__ void gram_f32_kernel(const float* __restrict__ x, int64_t n_tok, int6
 constexpr int GQ_ROWS = 128;   // rows of G per workgroup of the products
 constexpr int GQ_K = 32;       // contraction chunk staged in LDS
 // Workgroups (partial sums) of the column-Gram pass: a 64-column block's pass is a chain of 32-row
-// chunks on few compute units (13.5 us with 64,
-// 8.5 so at d = 4096), a wider one fills them by its column blocks.
+// chunks on few compute units (13.5 us with 64, 8.5 so at d = 4096), a wider one fills them by its
+// column blocks.
 constexpr int npart(int b) { return b <= 64 ? 128 : 64; }
 
 size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
