@@ -600,8 +600,10 @@ __global__ void __launch_bounds__(256, 2) attention_gqa_kernel(const uint16_t* _
   constexpr int VPT = 32 * KC / 256;   // V items (key pair x 8 columns) per thread and block
   // (Through buffer descriptors over the head's rows of this sequence: the per-lane part of an
   // address is formed once, a block adds a scalar; keys past the sequence read zeros, and their
-  // probabilities are 0.  The vector instructions bound the kernel - 28.6 to 22.8 million of them
-  // per launch at the shape above, 187 to 179 us - with the matrix cores busy 23% of the time.)
+  // probabilities are 0.  The row goes into the vector offset, which the bound is checked against:
+  // the scalar offset is taken off the bound first, and a ragged last block's would exceed it.
+  // The vector instructions bound the kernel - 28.6 to 22.8 million of them per launch at the
+  // shape above, 187 to 179 us - with the matrix cores busy 23% of the time.)
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
   u32x4 kreg[KPT], vreg[VPT][2];
   const int kld = (int)ldk * 2, vld = (int)ldv * 2;
@@ -612,12 +614,12 @@ __global__ void __launch_bounds__(256, 2) attention_gqa_kernel(const uint16_t* _
   auto fetch = [&](int kb, bool with_v) {
 #pragma unroll
     for (int t = 0; t < KPT; ++t)
-      kreg[t] = __builtin_amdgcn_raw_buffer_load_b128(krs, ko, (kb * 64 + t * (256 / KC)) * kld, 0);
+      kreg[t] = __builtin_amdgcn_raw_buffer_load_b128(krs, ko + (kb * 64 + t * (256 / KC)) * kld, 0, 0);
     if (with_v) {
 #pragma unroll
       for (int t = 0; t < VPT; ++t) {
-        vreg[t][0] = __builtin_amdgcn_raw_buffer_load_b128(vrs, vo0 + t * 128, kb * 64 * vld, 0);
-        vreg[t][1] = __builtin_amdgcn_raw_buffer_load_b128(vrs, vo1 + t * 128, kb * 64 * vld, 0);
+        vreg[t][0] = __builtin_amdgcn_raw_buffer_load_b128(vrs, vo0 + kb * 64 * vld + t * 128, 0, 0);
+        vreg[t][1] = __builtin_amdgcn_raw_buffer_load_b128(vrs, vo1 + kb * 64 * vld + t * 128, 0, 0);
       }
     }
   };

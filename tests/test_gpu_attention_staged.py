@@ -17,11 +17,25 @@ pytestmark = pytest.mark.gpu
     (2, 129, 12, 3, 128), (1, 300, 16, 2, 64), (2, 511, 3, 3, 128), (1, 513, 8, 8, 64),
 ])
 def test_attention_staged(n_seq, seq, H, Hkv, hd):
-    announce("attention staged", n_seq, seq, H, Hkv, hd)
+    _check(n_seq, seq, H, Hkv, hd, 0)
+
+
+@pytest.mark.parametrize("n_seq,seq,H,Hkv,hd", [(1, 1, 8, 8, 128), (2, 65, 6, 3, 64), (1, 300, 40, 40, 128),
+                                                (1, 497, 16, 4, 128)])
+def test_attention_staged_rows_behind(n_seq, seq, H, Hkv, hd):
+    """Rows behind the last sequence, up to the end of its 64-key block, hold NaN: they count as
+    zeros with probability 0."""
+    _check(n_seq, seq, H, Hkv, hd, 64)
+
+
+def _check(n_seq, seq, H, Hkv, hd, behind):
+    announce("attention staged", n_seq, seq, H, Hkv, hd, behind)
     g = torch.Generator(device=dev())
     g.manual_seed(seq)
     n, a, b = n_seq * seq, H * hd, (H + Hkv) * hd
-    qkv = torch.randn(n, (H + 2 * Hkv) * hd, generator=g, device=dev()).to(torch.bfloat16)
+    buf = torch.full((n + behind, (H + 2 * Hkv) * hd), float("nan"), dtype=torch.bfloat16, device=dev())
+    qkv = buf[:n]
+    qkv.copy_(torch.randn(n, (H + 2 * Hkv) * hd, generator=g, device=dev()))
     out = torch.full((n, a), float("nan"), dtype=torch.bfloat16, device=dev())
     scale = 1.0 / math.sqrt(hd)
     Z.attention(qkv[:, :a], qkv[:, a:b], qkv[:, b:], out, n_seq, seq, H, Hkv, hd, scale)
