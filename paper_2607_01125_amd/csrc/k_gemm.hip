@@ -353,7 +353,8 @@ __global__ void __launch_bounds__(256) gemm_pm_f32_kernel(GemmArgsF32 a, int vec
   const int lr = lane & 15, lk = lane >> 4;
   const int half = (int)blockIdx.x / a.tiles_m_half;
   const int64_t m0 = (int64_t)((int)blockIdx.x % a.tiles_m_half) * 64 + (MI == 1 ? wave * 16 : (wave >> 1) * 32);
-  const int64_t n0 = (int64_t)blockIdx.y * TN + (MI == 1 ? 0 : (wave & 1) * 32);
+  // (feature tiles go on in z: y alone would end at 65,535 of them)
+  const int64_t n0 = ((int64_t)blockIdx.z * gridDim.y + blockIdx.y) * TN + (MI == 1 ? 0 : (wave & 1) * 32);
   if (m0 >= a.T || n0 >= a.N) return;   // (no barrier below)
   const float* xh = a.x + (int64_t)half * a.T * a.K;
   floatx4 acc[2][MI];
@@ -482,9 +483,10 @@ hipError_t launch_f32(GemmArgsF32 a, int halves, hipStream_t s) {
   const bool small = tiles_m * halves * ((a.N + 63) / 64) < 512;
   const int tn = small ? 32 : 64;
   const int64_t tiles_n = (a.N + tn - 1) / tn;
-  if (tiles_m * halves > 0x7FFFFFFF || tiles_n > 65535) return hipErrorInvalidValue;
+  const int64_t gy = tiles_n < 65535 ? tiles_n : 65535, gz = (tiles_n + gy - 1) / gy;
+  if (tiles_m * halves > 0x7FFFFFFF || gz > 65535) return hipErrorInvalidValue;
   a.tiles_m_half = (int32_t)tiles_m;
-  const dim3 grid((unsigned)(tiles_m * halves), (unsigned)tiles_n);
+  const dim3 grid((unsigned)(tiles_m * halves), (unsigned)gy, (unsigned)gz);
   const int vec = a.K % 4 == 0 && ((reinterpret_cast<uintptr_t>(a.x) | reinterpret_cast<uintptr_t>(a.w)) & 15) == 0;
   if (small) gemm_pm_f32_kernel<EPI, 1><<<grid, dim3(256), 0, s>>>(a, vec);
   else gemm_pm_f32_kernel<EPI, 2><<<grid, dim3(256), 0, s>>>(a, vec);

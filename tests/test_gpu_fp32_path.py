@@ -67,6 +67,20 @@ def test_linear_f32(T, K, N, r, flags, bias, resid, shift):
     assert err <= 2.0 ** -23 * (K + r) * np.sqrt(np.mean(ref ** 2)) + 1e-5, err
 
 
+def test_linear_f32_many_features():
+    """More 64-feature tiles than one grid dimension holds (65,535)."""
+    K, N = 4, 65535 * 64 + 33
+    announce("fp32 linear, many features", N)
+    g = torch.Generator(device=dev())
+    g.manual_seed(8)
+    x, w = torch.randn(2, K, generator=g, device=dev()), torch.randn(N, K, generator=g, device=dev())
+    y = torch.full((2, N), float("nan"), device=dev())
+    Z.linear_fwd_pm(Z.Linear(w, K, N), None, x, 1, None, y, Z.Pert(1, 1, 0, 0.0))
+    want = x.double() @ w.double().T
+    # a chain of four products: four roundings of at most half an ulp of sums below 4 x 36
+    assert float((y.double() - want).abs().max()) <= 4 * 2.0 ** -24 * 144
+
+
 # one query, a query group short of 8, keys across the 64-key steps, grouped heads, head sizes
 # below and above one column per lane, the longest sequence a head size allows
 @pytest.mark.parametrize("n_seq,seq,H,Hkv,hd", [(1, 1, 1, 1, 4), (3, 9, 4, 2, 32), (2, 65, 4, 4, 32), (2, 130, 2, 1, 30),
