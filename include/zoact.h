@@ -228,12 +228,19 @@ zoact_status zoact_gen_z(uint64_t seed, uint32_t step, uint32_t query, int64_t e
  * zoact_project_workspace_bytes(n_tok, d_in, r) bytes lets the depth be split over
  * workgroups as well (fewer U^T bytes per byte of x; fp32 partials, summed in a fixed
  * order by a second pass, so the same values on every run); calls that overlap on one
- * workspace race.  The split form is taken where it is the faster one (d_in > 4096 or
- * n_tok <= 4096); otherwise, with ws NULL or too small, the single-pass kernel (values
- * may differ from the split form in the last bit). */
+ * workspace race.  BF16 runs one of three forms, whose values may differ in the last bit:
+ *  - few tokens: n_tok <= 2048 and (r <= 64 or ceil(n_tok / 16) ceil(r / 32) <= 256); its depth
+ *    in chunks with ws;
+ *  - split: with ws, where d_in > 4096 or n_tok <= 4096;
+ *  - single pass: all else (ws NULL, too small or unused).
+ * zoact_project_part computes n_tok rows of a batch of n_all rows: the form, and so every bit
+ * of p, is that of zoact_project over all n_all rows with a workspace of that kind
+ * (n_all >= n_tok; ws as for n_tok rows). */
 size_t zoact_project_workspace_bytes(int64_t n_tok, int64_t d_in, int32_t r);
 zoact_status zoact_project(const void* x, int32_t dtype, int64_t n_tok, int64_t d_in, const void* ut,
                            int32_t r, void* p, void* ws, size_t ws_bytes, zoact_stream stream);
+zoact_status zoact_project_part(const void* x, int32_t dtype, int64_t n_tok, int64_t n_all, int64_t d_in,
+                                const void* ut, int32_t r, void* p, void* ws, size_t ws_bytes, zoact_stream stream);
 
 /* The projection of a site whose input is a norm's output (the attention and MLP inputs
  * of a decoder layer), fused with that norm: y = RMSNorm(x) * w, or LayerNorm(x) * w + b,

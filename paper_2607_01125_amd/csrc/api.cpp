@@ -81,17 +81,24 @@ size_t zoact_project_workspace_bytes(int64_t n_tok, int64_t d_in, int32_t r) {
 
 zoact_status zoact_project(const void* x, int32_t dtype, int64_t n_tok, int64_t d_in, const void* ut, int32_t r, void* p,
                            void* ws, size_t ws_bytes, zoact_stream stream) {
+  return zoact_project_part(x, dtype, n_tok, n_tok, d_in, ut, r, p, ws, ws_bytes, stream);
+}
+
+zoact_status zoact_project_part(const void* x, int32_t dtype, int64_t n_tok, int64_t n_all, int64_t d_in,
+                                const void* ut, int32_t r, void* p, void* ws, size_t ws_bytes, zoact_stream stream) {
   CHECK(float_type(dtype), "project: dtype must be F32 or BF16");
   CHECK(n_tok >= 1 && d_in >= 1, "project: empty shape (n_tok=%lld, d_in=%lld)", (long long)n_tok, (long long)d_in);
+  CHECK(n_all >= n_tok, "project: n_all=%lld < n_tok=%lld", (long long)n_all, (long long)n_tok);
   CHECK(r >= 1 && r <= 256, "project: r=%d outside [1, 256]", r);
   CHECK(x && ut && p, "project: NULL pointer");
   if (dtype == ZOACT_BF16) {
     CHECK(d_in % 32 == 0, "project: bf16 needs d_in %% 32 == 0 (d_in=%lld)", (long long)d_in);
     CHECK(aligned16(x) && aligned16(ut), "project: x and ut must be 16-byte aligned");
     const bool split = ws && r <= 64 && ws_bytes >= zoact::project_ws_bytes(n_tok, d_in, r) &&
-                       (d_in > 4096 || n_tok <= 4096);
+                       (d_in > 4096 || n_all <= 4096);
     if (split) CHECK(aligned16(ws), "project: ws must be 16-byte aligned");
-    const hipError_t few = zoact::launch_project_few(x, n_tok, d_in, ut, r, p, split ? ws : nullptr, st(stream));
+    const hipError_t few = zoact::launch_project_few(x, n_tok, n_all, d_in, ut, r, p, split ? ws : nullptr,
+                                                      st(stream));
     if (few != hipErrorNotSupported) return hip_status(few, "project");
     // the depth-split form where it measured faster: deep inputs, or few tokens (at
     // 8192 x 4096 the single pass is level with it)

@@ -34,9 +34,10 @@ hipError_t launch_dequant_int4(const void* w, const void* scales, int64_t d_out,
 size_t project_ws_bytes(int64_t n_tok, int64_t d_in, int32_t r);
 hipError_t launch_project_split(const void* x, int64_t n_tok, int64_t d_in, const void* ut, int32_t r, void* p,
                                 void* ws, hipStream_t s);
-// ws (project_ws_bytes) or null: no depth chunks; hipErrorNotSupported where the other forms are used.
-hipError_t launch_project_few(const void* x, int64_t n_tok, int64_t d_in, const void* ut, int32_t r, void* p,
-                              void* ws, hipStream_t s);
+// ws (project_ws_bytes) or null: no depth chunks; hipErrorNotSupported where a batch of n_all tokens
+// uses the other forms.
+hipError_t launch_project_few(const void* x, int64_t n_tok, int64_t n_all, int64_t d_in, const void* ut, int32_t r,
+                              void* p, void* ws, hipStream_t s);
 hipError_t launch_project(const void* x, int32_t dtype, int64_t n_tok, int64_t d_in, const void* ut, int32_t r,
                           void* p, hipStream_t s);
 // Norm (RMSNorm, or LayerNorm with bias b) of n_tok rows and the projection of its output,

@@ -1146,29 +1146,24 @@ hipError_t launch_project_split(const void* x, int64_t n_tok, int64_t d_in, cons
 
 // The few-token form, up to 2048 tokens; else, and where its tiles would fill the chip more
 // than once (more of them only share the L2 -> CU rate with larger tiles' fewer bytes),
-// hipErrorNotSupported.  With a workspace the depth goes in up to four chunks, by d_in alone, so
-// that P's bits do not depend on the tokens beside a row (a shared input is projected over half
-// the rows of the stacked one).  Kernel times at 512 tokens, chunks + sum against one pass:
-// d_in = 4096, r = 32: 4.8 + 2.3 against 9.8 us.  Whole calls at 32 to 2048 tokens against the
-// forms below (us): 14336: 11-19 (19-25), 20480 at r = 64: 13-44 (34-46); at 4096 tokens level
-// or slower.
-hipError_t launch_project_few(const void* x, int64_t n_tok, int64_t d_in, const void* ut, int32_t r, void* p,
-                              void* ws, hipStream_t s) {
-  if (n_tok > 2048) return hipErrorNotSupported;
+// hipErrorNotSupported.  With a workspace the depth goes in up to four chunks, by d_in alone, and
+// neither the tile nor the tokens beside a row change the order of its sums: P's bits depend on
+// the form only, which the batch of n_all rows decides (a shared input is projected over half the
+// rows of the stacked one, with the same bits).  Kernel times at 512 tokens, chunks + sum against
+// one pass: d_in = 4096, r = 32: 4.8 + 2.3 against 9.8 us.  Whole calls at 32 to 2048 tokens
+// against the forms below (us): 14336: 11-19 (19-25), 20480 at r = 64: 13-44 (34-46); at 4096
+// tokens level or slower.
+hipError_t launch_project_few(const void* x, int64_t n_tok, int64_t n_all, int64_t d_in, const void* ut, int32_t r,
+                              void* p, void* ws, hipStream_t s) {
+  if (n_all > 2048) return hipErrorNotSupported;
   const int ns = ws ? project_nsplit(d_in) : 1;
-  auto wgs = [&](int t, int c) -> int64_t {
-    return (n_tok + 16 * t - 1) / (16 * t) * ((r + 16 * c - 1) / (16 * c)) * ns;
+  auto wgs = [&](int64_t n, int t, int c) -> int64_t {
+    return (n + 16 * t - 1) / (16 * t) * ((r + 16 * c - 1) / (16 * c)) * ns;
   };
+  if (wgs(n_all, 1, 2) > 256 && (ns == 1 || wgs(n_all, 2, 2) > 512)) return hipErrorNotSupported;
   // the smallest tile that fits one round of the chip (two for the largest, whose workgroups
   // are short with the depth in chunks)
-  int tb = 1, cb = 1;
-  if (wgs(1, 1) > 256) {
-    cb = 2;
-    if (wgs(1, 2) > 256) {
-      tb = 2;
-      if (ns == 1 || wgs(2, 2) > 512) return hipErrorNotSupported;
-    }
-  }
+  const int cb = wgs(n_tok, 1, 1) > 256 ? 2 : 1, tb = wgs(n_tok, 1, 2) > 256 ? 2 : 1;
   const int64_t chunk = ((d_in + ns - 1) / ns + 63) / 64 * 64;
   const dim3 grid((unsigned)((n_tok + 16 * tb - 1) / (16 * tb)), (unsigned)((r + 16 * cb - 1) / (16 * cb)), (unsigned)ns);
   const auto* xx = static_cast<const uint16_t*>(x);

@@ -307,10 +307,11 @@ class Decoder:
         return self._rope[seq]
 
     # ---------------------------------------------------------------- forward of both halves
-    def _norm_site(self, l, site, x, w, b, y, adapt, calibrate):
+    def _norm_site(self, l, site, x, w, b, y, adapt, calibrate, rows):
         """The norm of x into y, then the site's projection of y into P (U^T of the site, or
-        None where it is not adapted); one fused pass where the library covers it."""
-        if (adapt and self.fuse_norm_project and NORM_PROJECT_ROWS[0] <= x.shape[0] <= NORM_PROJECT_ROWS[1]
+        None where it is not adapted); one fused pass where the library covers it.  The forms
+        are those of `rows` rows, the forward's 2 T, also where x is one half of them."""
+        if (adapt and self.fuse_norm_project and NORM_PROJECT_ROWS[0] <= rows <= NORM_PROJECT_ROWS[1]
                 and (l, site) in self._adapted_sites):
             ut = self.ut.get((l, site))
             if ut is None:
@@ -322,7 +323,7 @@ class Decoder:
                 Z.layernorm_project(x, w, b, y, self.s.norm_eps, ut, p)
             return ut
         self._norm(x, w, b, y)
-        return self._site(l, site, y, adapt, calibrate)
+        return self._site(l, site, y, adapt, calibrate, rows)
 
     def _norm(self, x, w, b, y):
         if self.s.family == "llama":
@@ -406,21 +407,23 @@ class Decoder:
         for l, P in enumerate(self.layers):
             # attention block.  Layer 0 of a forward whose halves read the same tokens: both
             # halves' inputs are the same embedding rows, so the norm and the projection run
-            # on one half and the fused q|k|v forms x W^T once (the same bits as stacked)
+            # on one half and the fused q|k|v forms x W^T once.  The same bits as stacked,
+            # save where the stacked GEMM splits a partly idle last round by depth, which the
+            # shared-input form does not (Llama-3-8B's q|k|v: 1793 to 2048 tokens per half)
             qkv = B["qkv"]
             shared = (l == 0 and adapt and not distinct_halves and "qkv" in P
                       and self._shared_ok(P["qkv"], self.ut.get((0, "attn")), T))
             if shared:
                 a1 = B["a"][:T]
-                ut = self._norm_site(l, "attn", h[:T], P["n1"], P.get("n1b"), a1, adapt, calibrate)
+                ut = self._norm_site(l, "attn", h[:T], P["n1"], P.get("n1b"), a1, adapt, calibrate, 2 * T)
                 self._apply(P["qkv"], a1, T, qkv, pert, ut, flags=Z.SHARED_X, adapt=adapt)
                 q, k, v = qkv[:, :d], qkv[:, d:d + dkv], qkv[:, d + dkv:]
             elif "qkv" in P:
-                ut = self._norm_site(l, "attn", h, P["n1"], P.get("n1b"), B["a"], adapt, calibrate)
+                ut = self._norm_site(l, "attn", h, P["n1"], P.get("n1b"), B["a"], adapt, calibrate, 2 * T)
                 self._apply(P["qkv"], B["a"], T, qkv, pert, ut, adapt=adapt)
                 q, k, v = qkv[:, :d], qkv[:, d:d + dkv], qkv[:, d + dkv:]
             else:
-                ut = self._norm_site(l, "attn", h, P["n1"], P.get("n1b"), B["a"], adapt, calibrate)
+                ut = self._norm_site(l, "attn", h, P["n1"], P.get("n1b"), B["a"], adapt, calibrate, 2 * T)
                 self._apply(P["qv"], B["a"], T, qkv, pert, ut, adapt=adapt)
                 self._apply(P["k"], B["a"], T, B["k"], pert, None, adapt=False)
                 q, k, v = qkv[:, :d], B["k"], qkv[:, d:]
@@ -433,7 +436,7 @@ class Decoder:
             self._apply(P["o"], B["att"], T, h_alt, pert, ut, residual=h, adapt=adapt)
             h, h_alt = h_alt, h
             # MLP block
-            ut = self._norm_site(l, "mlp", h, P["n2"], P.get("n2b"), B["a"], adapt, calibrate)
+            ut = self._norm_site(l, "mlp", h, P["n2"], P.get("n2b"), B["a"], adapt, calibrate, 2 * T)
             flags = Z.EPI_SWIGLU if s.family == "llama" else Z.EPI_RELU
             self._apply(P["gu"], B["a"], T, B["ff"], pert, ut, flags=flags, adapt=adapt)
             ut = self._site(l, "down", B["ff"], adapt, calibrate)
@@ -447,8 +450,9 @@ class Decoder:
         Z.linear_fwd_pm(self.head, None, B["a"], T, None, B["logits"], pert)
         return B["logits"].view(2, n_seq, seq, s.vocab)
 
-    def _site(self, l, site, x, adapt, calibrate):
-        """U^T of an adapted site after projecting its input into P (None if not adapted)."""
+    def _site(self, l, site, x, adapt, calibrate, rows=None):
+        """U^T of an adapted site after projecting its input into P (None if not adapted), in the
+        projection's form for `rows` rows (x's own)."""
         if not adapt:
             calibrate(l, site, x)
             return None
@@ -461,7 +465,7 @@ class Decoder:
         need = Z.project_workspace_bytes(n_tok, x.shape[1], self.r) if self.act == torch.bfloat16 else 0
         if need and (self._proj_ws is None or self._proj_ws.numel() < need):
             self._proj_ws = torch.empty(need, dtype=torch.uint8, device=self.dev)
-        Z.project(x, ut, self._cur["p"][:n_tok], self._proj_ws if need else None)
+        Z.project(x, ut, self._cur["p"][:n_tok], self._proj_ws if need else None, n_all=rows)
         return ut
 
     def site_dims(self):

@@ -91,6 +91,7 @@ SIGNATURES = {
     "zoact_gen_z": ([_U64, _U32, _U32, _I64, _I64, _P, _P], _I32),
     "zoact_project_workspace_bytes": ([_I64, _I64, _I32], _SZ),
     "zoact_project": ([_P, _I32, _I64, _I64, _P, _I32, _P, _P, _SZ, _P], _I32),
+    "zoact_project_part": ([_P, _I32, _I64, _I64, _I64, _P, _I32, _P, _P, _SZ, _P], _I32),
     "zoact_rmsnorm_project": ([_P, _P, _I64, _I64, _F, _P, _I32, _P, _P, _P], _I32),
     "zoact_layernorm_project": ([_P, _P, _P, _I64, _I64, _F, _P, _I32, _P, _P, _P], _I32),
     "zoact_linear_fwd_pm": ([ctypes.POINTER(LinearDesc), ctypes.POINTER(ArenaDesc), _P, _I32, _I64, _P, _P, _U32,
@@ -236,13 +237,15 @@ def project_workspace_bytes(n_tok: int, d_in: int, r: int) -> int:
     return int(lib().zoact_project_workspace_bytes(n_tok, d_in, r))
 
 
-def project(x: torch.Tensor, ut: torch.Tensor, p: torch.Tensor, ws: torch.Tensor | None = None, stream=None):
-    """p = x U; with a workspace `ws` (project_workspace_bytes) the depth-split form."""
+def project(x: torch.Tensor, ut: torch.Tensor, p: torch.Tensor, ws: torch.Tensor | None = None, stream=None,
+            n_all: int | None = None):
+    """p = x U; with a workspace `ws` (project_workspace_bytes) the depth-split forms.  `n_all`: the
+    rows of the batch that x is a part of (its form, so the bits the whole batch would give)."""
     d_in = x.shape[-1]
     n_tok = x.numel() // d_in
     nb = ws.numel() * ws.element_size() if ws is not None else 0
-    _check(lib().zoact_project(_ptr(x), dtype_code(x), n_tok, d_in, _ptr(ut), ut.shape[0], _ptr(p), _ptr(ws), nb,
-                               _stream(stream)))
+    _check(lib().zoact_project_part(_ptr(x), dtype_code(x), n_tok, n_tok if n_all is None else n_all, d_in, _ptr(ut),
+                                    ut.shape[0], _ptr(p), _ptr(ws), nb, _stream(stream)))
 
 
 def rmsnorm_project(x: torch.Tensor, w: torch.Tensor, y: torch.Tensor, eps: float, ut: torch.Tensor, p: torch.Tensor,

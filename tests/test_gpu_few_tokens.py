@@ -138,7 +138,7 @@ def test_few_tokens_small_workspace(ws_kb):
 # four chunks with a ragged last one, ranks off the 16-column tiles
 @pytest.mark.parametrize("n,d,r", [(1, 32, 1), (17, 96, 16), (33, 1056, 5), (512, 4096, 32), (1025, 4096, 33),
                                    (2048, 4096, 32), (700, 8224, 64), (2047, 14336, 32), (100, 5120, 100),
-                                   (2049, 1024, 8)])
+                                   (2049, 1024, 8), (2560, 3072, 16), (2560, 5120, 32), (4098, 4096, 32)])
 @pytest.mark.parametrize("use_ws", [False, True])
 def test_project_few_tokens(n, d, r, use_ws):
     announce("project few tokens", n, d, r, use_ws)
@@ -149,7 +149,12 @@ def test_project_few_tokens(n, d, r, use_ws):
     Z.project(x, ut, p, ws)
     assert_bf16_close(host(p), (x.double() @ ut.double().T).cpu().numpy(), what="project, few tokens")
     assert torch.all(guard[0] == 3.0) and torch.all(guard[n + 1] == 3.0)
-    # a row's bits do not depend on the rows beside it while both calls are of this form
+    # a row's bits do not depend on the rows beside it: one half computed as part of the whole
+    for n2 in {n // 2, (n + 1) // 2} - {0}:
+        part = torch.full((n2, r), float("nan"), dtype=torch.bfloat16, device=dev())
+        Z.project(x[:n2], ut, part, ws, n_all=n)
+        assert torch.equal(part.view(torch.int16), p[:n2].contiguous().view(torch.int16))
+    # nor while both calls are of this form
     if 1 < n <= 1024 and r <= 64:
         half = torch.empty(n // 2, r, dtype=torch.bfloat16, device=dev())
         Z.project(x[:n // 2], ut, half, ws)

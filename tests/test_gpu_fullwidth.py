@@ -170,13 +170,15 @@ def test_llama_full_width_resident_attention(llama_bf16):
         _logits_close(got[h], want, 2e-2, f"resident attention half {h}")
 
 
-def test_llama_full_width_shared_first_layer_bitwise(llama_bf16):
+@pytest.mark.parametrize("n_seq", [4, 5])
+def test_llama_full_width_shared_first_layer_bitwise(llama_bf16, n_seq):
     """The first projection in its shared-input form gives the same logits, bit for bit,
-    as the stacked form (both halves fed the same embedding rows twice)."""
+    as the stacked form (both halves fed the same embedding rows twice), on both sides of the
+    2048 rows from which the norm and the projection take other forms."""
     _, g = llama_bf16
-    tok = t_i32(synth.uniform_tokens(4, 256, g.s.vocab, 23, 4))
+    tok = t_i32(synth.uniform_tokens(n_seq, 256, g.s.vocab, 23, 4))
     pert = Z.Pert(8, 4, 0, 1e-2)
-    announce("llama full width shared first layer")
+    announce("llama full width shared first layer", n_seq)
     g.shared_first = True
     a = g.forward(tok, pert).clone()
     g.shared_first = False
