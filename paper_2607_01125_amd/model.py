@@ -46,9 +46,10 @@ import torch
 from . import zoact as Z
 
 SITES = ("attn", "o", "mlp", "down")
-# widths and row counts at which the decoder forms a norm and its site's projection in one pass
-NORM_PROJECT_WIDTHS = (128, 256, 512, 1024, 2048, 4096)
-NORM_PROJECT_ROWS = (2049, 4096)
+# widths covered by zoact_rmsnorm_project / zoact_layernorm_project, and the largest row count at
+# which the decoder uses them
+NORM_PROJECT_WIDTHS = (128, 256, 512, 1024, 2048, 4096, 5120)
+NORM_PROJECT_MAX_ROWS = 4096
 # largest tokens per half at which INT4 layers run on their packed weights
 INT4_PACKED_MAX_TOKENS = 256
 
@@ -99,6 +100,40 @@ def _pair_key(pert) -> tuple:
     """(seed, step, queries, signs, eps) of a Pert or PertPair."""
     pp = Z.as_pair(pert)
     return (pp.seed, pp.step, tuple(pp.query), tuple(pp.sign), float(pp.eps))
+
+
+def norm_project_pays(layernorm: bool, rows: int, d: int, r: int) -> bool:
+    """Whether a norm of `rows` rows of width d and the rank-r projection of its output run as one
+    fused pass.
+
+    The fused pass's workgroups of 16 rows each walk the whole of U^T, so its time is bound by
+    d r; apart, the norm and the projection cost two or three launches.  Kernel times on MI355X
+    (us, fused / apart, RMSNorm; the row counts are the forward's 2 T):
+      d     r    512 rows     1024         2048         2560         4096
+      128   32   3.3 / 5.1    3.4 / 5.3    3.4 / 5.8    3.4 / 9.7    3.4 / 10.6
+      512   64   5.5 / 6.1    5.6 / 6.6    5.8 / 8.2    5.9 / 15.5   6.2 / 17.5
+      512   128  7.9 / 6.2    8.0 / 7.2    8.3 / 12.9   8.4 / 14.0   8.9 / 15.9
+      1024  32   6.6 / 7.7    6.7 / 8.6    7.1 / 10.0   7.4 / 18.6   8.0 / 21.4
+      1024  64   8.5 / 7.7    8.7 / 8.6    9.0 / 11.0   9.2 / 21.4   9.8 / 24.1
+      2048  32   10.9 / 9.3   11.2 / 10.5  12.0 / 14.0  12.4 / 19.4  15.1 / 20.2
+      2048  64   14.8 / 9.1   15.1 / 11.3  16.1 / 15.3  16.5 / 22.6  18.8 / 23.5
+      4096  32   19.9 / 10.9  20.6 / 14.1  23.2 / 19.9  22.4 / 21.3  25.0 / 25.4
+      4096  64   26.5 / 11.5  27.9 / 15.8  31.3 / 26.1  30.7 / 24.0  33.7 / 29.0
+      5120  64   33.8 / 17.3  34.1 / 23.8  39.9 / 35.0  40.4 / 44.0  42.6 / 50.9
+    LayerNorm's fused pass is dearer: 8.0 / 7.5 at 1024, r = 32 and 512 rows, 17.5 / 21.7 at 2048,
+    r = 32 and 4096, slower throughout at 4096 (28.5 / 23.1 at r = 32, 2560 rows) and 5120.
+    """
+    if rows > NORM_PROJECT_MAX_ROWS or d not in NORM_PROJECT_WIDTHS or r > 128:
+        return False
+    # the few-token projection, which the norm's output still finds in the caches
+    if rows <= 2048 and (r <= 64 or -(-rows // 16) * -(-r // 32) <= 256):
+        m = 2 if rows > 1024 else 1
+        if layernorm:
+            return d * r <= 32768 and d <= 512 * m
+        return (d * r <= 32768 * m and d <= 1024 * m) or (d == 5120 and r <= 16 and m == 2)
+    if layernorm:
+        return d <= 2048
+    return d != 4096 or r <= 32 or r > 64
 
 
 def interleave_gate_up(wg: torch.Tensor, wu: torch.Tensor) -> torch.Tensor:
@@ -168,15 +203,8 @@ class Decoder:
         # and x U once (ZOACT_SHARED_X) when the layer qualifies
         self.shared_first = True
         # norms that feed an adapted site (attention and MLP inputs) also form the site's
-        # projection P = x U in the same pass where the library covers the width and it is
-        # the faster form.  Kernel times on MI355X at d = 4096, r = 32 (RMSNorm), fused
-        # against norm + projection: 512 rows 19.6 against 11 us, 2048 rows 22.8 against
-        # 18.7, 4096 rows 24.8 against 27, 8192 rows 42 against 39.6: its workgroups of 16
-        # tokens each walk the whole of U^T and read their rows twice, which only pays while
-        # the norm alone leaves the chip part idle and the rows outgrow the few-token
-        # projection.  LayerNorm at d = 5120, r = 64 is slower fused throughout (39 against
-        # 14 us at 512 rows, 48.6 against 36 at 4096).
-        self.fuse_norm_project = mode != "fp32" and self.r <= 32 and self.d in NORM_PROJECT_WIDTHS
+        # projection P = x U in the same pass where that is the faster form
+        self.fuse_norm_project = mode != "fp32"
         # INT4 layers: True dequantises each layer once per forward into one bf16 buffer (the
         # largest layer's size, allocated on first use) and runs the bf16 schedule, from more
         # than INT4_PACKED_MAX_TOKENS tokens per half; False always keeps the GEMMs that read
@@ -311,8 +339,8 @@ class Decoder:
         """The norm of x into y, then the site's projection of y into P (U^T of the site, or
         None where it is not adapted); one fused pass where the library covers it.  The forms
         are those of `rows` rows, the forward's 2 T, also where x is one half of them."""
-        if (adapt and self.fuse_norm_project and NORM_PROJECT_ROWS[0] <= rows <= NORM_PROJECT_ROWS[1]
-                and (l, site) in self._adapted_sites):
+        if (adapt and self.fuse_norm_project and (l, site) in self._adapted_sites
+                and norm_project_pays(self.s.family != "llama", rows, self.d, self.r)):
             ut = self.ut.get((l, site))
             if ut is None:
                 raise RuntimeError(f"no basis for site {(l, site)}: run basis_init or set_basis first")
