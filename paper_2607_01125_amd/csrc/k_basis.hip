@@ -1168,8 +1168,11 @@ __global__ void __launch_bounds__(256) jacobi_kernel(const double* __restrict__ 
 // registers between the pair's dot products and its update (8 BP threads: several waves
 // per SIMD hide each other's latency); one barrier per round.  A pair rotates when
 // |a_p . a_q| > 1e-15 ||a_p|| ||a_q||; the sweeps stop once the largest such ratio a sweep met
-// is at most 1e-9: they converge quadratically, so what is left after that sweep is below
-// rounding (1e-13 spent one more sweep, of seven, on the same result).
+// is at most 1e-13, or at most 1e-9 with rotations so small that ratio times largest tangent is at
+// most 1e-15.  What a sweep leaves is of the order of that product: for separated values the
+// tangent is about the ratio, and a sweep at 1e-9 is the last (1e-13 alone spent one more, of
+// seven, on the same result); among values that agree to about the ratio the rotations stay
+// large, and stopping on the ratio alone left columns orthogonal to 6e-10 only.
 //
 // One workgroup, so a round's serial chain bounds it: the dot products' sums over the 16 lanes
 // run in the vector unit (row rotations) and the rotation is three reciprocal (square root)
@@ -1194,7 +1197,7 @@ __global__ void __launch_bounds__(8 * BP) jacobi1s_kernel(const double* __restri
   constexpr int LD = BP + 1, G = 16, RPL = BP / G, NT = 8 * BP, NW = NT / 64;
   __shared__ double A[BP * LD];
   __shared__ double nrm[BP];
-  __shared__ double wmax[NW];
+  __shared__ double wmax[NW], tmax[NW];
   const int t = threadIdx.x, grp = t / G, gl = t % G;
   const int n = (b + 1) & ~1;
   for (int e = t; e < BP * BP; e += NT) {
@@ -1203,7 +1206,7 @@ __global__ void __launch_bounds__(8 * BP) jacobi1s_kernel(const double* __restri
   }
   __syncthreads();
   for (int sw = 0; sw < sweeps; ++sw) {
-    double worst = 0.0;
+    double worst = 0.0, wtan = 0.0;   // largest ratio and tangent, squared
     for (int round = 0; round < n - 1; ++round) {
       if (grp < n / 2) {
         int p, q;
@@ -1247,6 +1250,7 @@ __global__ void __launch_bounds__(8 * BP) jacobi1s_kernel(const double* __restri
             const double h = h2 > 1e-280 ? h2 * rsqrt_nr(h2) : 0.0;
             const double den = fabs(d) + h;
             const double tq = den > 1e-140 ? (d >= 0 ? g2 : -g2) * rcp_nr(den) : (ga >= 0 ? 1.0 : -1.0);
+            wtan = fmax(wtan, tq * tq);
             const double cc = rsqrt_nr(fma(tq, tq, 1.0)), ss = tq * cc;
 #pragma unroll
             for (int k = 0; k < RPL; ++k) {
@@ -1259,14 +1263,17 @@ __global__ void __launch_bounds__(8 * BP) jacobi1s_kernel(const double* __restri
       __syncthreads();
     }
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) worst = fmax(worst, __shfl_xor(worst, o, 64));
-    if ((t & 63) == 0) wmax[t >> 6] = worst;
+    for (int o = 1; o < 64; o <<= 1) {
+      worst = fmax(worst, __shfl_xor(worst, o, 64));
+      wtan = fmax(wtan, __shfl_xor(wtan, o, 64));
+    }
+    if ((t & 63) == 0) wmax[t >> 6] = worst, tmax[t >> 6] = wtan;
     __syncthreads();
-    double w = 0.0;
+    double w = 0.0, tn = 0.0;
 #pragma unroll
-    for (int q = 0; q < NW; ++q) w = fmax(w, wmax[q]);
+    for (int q = 0; q < NW; ++q) w = fmax(w, wmax[q]), tn = fmax(tn, tmax[q]);
     __syncthreads();
-    if (w <= 1e-18) break;   // (squares: a ratio of 1e-9)
+    if (w <= 1e-26 || (w <= 1e-18 && w * tn <= 1e-30)) break;   // (squares)
   }
   if (t < b) {
     double s2 = 0.0;
