@@ -55,8 +55,9 @@ __device__ __forceinline__ float f32_bits(uint32_t b) { return __uint_as_float(b
 // n / d and sqrt(x) for this generator's operands, correctly rounded without the range scaling
 // and special cases of the general forms: a reciprocal (square root) estimate, one refinement,
 // and one step on the exact residual.  d is in [1.7, 2.5) and |n| < 0.42; x is 0 (of either sign,
-// returned as it is) or in [1e-7, 34).  Both depend only on the 24 bits of a uniform: the results
-// equal the IEEE operations' for all 2^24 of them (checked on the device).
+// returned as it is) or in [1e-7, 34).  Both depend only on the 24 bits of a uniform: any estimate
+// within a unit of the last place gives the IEEE operations' result for all 2^24 of them but six,
+// for which this device's estimates give it too (tests/test_rng_short_division.py).
 __device__ __forceinline__ float div_small(float n, float d) {
   float r = __builtin_amdgcn_rcpf(d);
   r = __builtin_fmaf(__builtin_fmaf(-d, r, 1.0f), r, r);
