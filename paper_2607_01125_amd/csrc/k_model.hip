@@ -274,8 +274,13 @@ __global__ void rope_kernel(T* __restrict__ x, int64_t rows, int64_t ld, int64_t
 // lane per value column walks the keys.  The operations of each output and their order are those
 // of the plain loop over keys (score, running maximum, rescale, accumulate; fused multiply-adds
 // as written).  (One thread per query walking all keys took 398 us at 8 sequences of 64, 4 heads
-// of 32: 256 dependent threads on 32 compute units, the output row in scratch memory; now 12.)
+// of 32: 256 dependent threads on 32 compute units, the output row in scratch memory; now 13.  At
+// 8 columns, 512 sequences of 512, where the threads fill the chip: 1710 then, 1415 now.)
 constexpr int F32_QPB = 8;
+// Lane l's value, l the same in every lane (no trip through LDS as with a shuffle).
+__device__ __forceinline__ float read_lane(float v, int l) {
+  return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(v), l));
+}
 __global__ void __launch_bounds__(256) attention_f32_kernel(const float* __restrict__ q, int64_t ldq, const float* __restrict__ k,
                                                             int64_t ldk, const float* __restrict__ v, int64_t ldv, int64_t seq,
                                                             int heads, int kv_heads, int hd, float scale,
@@ -316,13 +321,22 @@ __global__ void __launch_bounds__(256) attention_f32_kernel(const float* __restr
       const float before = __shfl_up(mk, 1, 64);
       const float ak = expf((lane ? before : m) - mk), pk = expf(fmaf(scale, dot, -mk));
       const int nk = sq + 1 - k0 < 64 ? sq + 1 - k0 : 64;
+      // (lanes past the columns read column 0 and are not stored: without a branch the reads of
+      // several keys are in flight)
+      const float* const vl = vs + k0 * hd + (lane < hd ? lane : 0);
+#pragma unroll 8
       for (int j = 0; j < nk; ++j) {
-        const float a = __shfl(ak, j, 64), p = __shfl(pk, j, 64);
+        const float a = read_lane(ak, j), p = read_lane(pk, j);
         l = fmaf(l, a, p);
-        if (lane < hd) acc[0] = fmaf(a, acc[0], __fmul_rn(p, vs[(k0 + j) * hd + lane]));
-        if (lane + 64 < hd) acc[1] = fmaf(a, acc[1], __fmul_rn(p, vs[(k0 + j) * hd + lane + 64]));
+        acc[0] = fmaf(a, acc[0], __fmul_rn(p, vl[j * hd]));
       }
-      m = __shfl(mk, nk - 1, 64);
+      if (hd > 64) {
+        const float* const vh = vs + k0 * hd + (lane + 64 < hd ? lane + 64 : 0);
+#pragma unroll 8
+        for (int j = 0; j < nk; ++j)
+          acc[1] = fmaf(read_lane(ak, j), acc[1], __fmul_rn(read_lane(pk, j), vh[j * hd]));
+      }
+      m = read_lane(mk, nk - 1);
     }
     float* o = out + (r0 + sq) * (int64_t)heads * hd + (int64_t)h * hd;
     if (lane < hd) o[lane] = acc[0] / l;
