@@ -6,6 +6,8 @@
 // (64-query block, head, sequence), scores and P.V on v_mfma_f32_16x16x32_bf16, a
 // two-pass softmax in fp32 with wave64 shuffles, K and V staged through LDS (V
 // transposed so that each lane's fragment holds 8 consecutive keys).
+#include <type_traits>
+
 #include <math.h>
 #include <stdio.h>
 
@@ -547,10 +549,14 @@ __global__ void __launch_bounds__(256, 2) attention_gqa_kernel(const uint16_t* _
   // (head, query tile), a head's longest (last) tiles first, so that the tiles that read the same
   // K and V do it through one L2: 198 us dealt in turn, 187 so at 16 x 512 tokens and 40 heads,
   // 146 and 112 with 32 / 8 heads.
-  const int n_wg = gridDim.x * gridDim.y;
-  int id = (int)blockIdx.x + (int)gridDim.x * (int)blockIdx.y;
-  if ((n_wg & 7) == 0) id = (id & 7) * (n_wg >> 3) + (id >> 3);
-  const int by = id / (int)gridDim.x, bx = (int)gridDim.x - 1 - (id - by * (int)gridDim.x), bz = blockIdx.z;
+  const int gx = gridDim.x, n_wg = gx * (int)gridDim.y, bz = blockIdx.z;
+  int by = blockIdx.y, bx = blockIdx.x;
+  if ((n_wg & 7) == 0) {
+    const int id = bx + gx * by, to = (id & 7) * (n_wg >> 3) + (id >> 3);
+    by = gx == 1 ? to : to / gx;
+    bx = to - by * gx;
+  }
+  bx = gx - 1 - bx;
   const int G = heads / kv_heads;
   const int HG = G < 4 ? G : 4;
   const int QT = 64 * QB / HG;                             // queries per workgroup tile
@@ -598,11 +604,11 @@ __global__ void __launch_bounds__(256, 2) attention_gqa_kernel(const uint16_t* _
     return (int)(last - (int64_t)kb * 64);
   };
 
-  // a key block needs the causal mask only where it reaches past the q-block's first query
-  // (or past the sequence); the test is uniform over the wave
-  auto masked = [&](int b, int kb) {
-    return (int64_t)kb * 64 + 63 > (q0 + b * 16 < seq - 1 ? q0 + b * 16 : seq - 1);
-  };
+  // a key block needs the causal mask only where it reaches past the wave's first query (or past
+  // the sequence); the test is uniform over the wave, one for all q-blocks, and both passes' bodies
+  // are straight-line code with and without the mask (a test per 16 keys and q-block kept the
+  // scores' chains apart: 165 us at 16 x 512 tokens and 40 heads, 153 so)
+  auto masked = [&](int kb) { return (int64_t)kb * 64 + 63 > (q0 < seq - 1 ? q0 : seq - 1); };
   // pass 1: row maxima of the raw scores over visible keys (scaling by a positive constant
   // keeps the maximiser, so the scale is applied once, to the maximum)
   float mq[QB];
@@ -616,8 +622,9 @@ __global__ void __launch_bounds__(256, 2) attention_gqa_kernel(const uint16_t* _
   // address is formed once, a block adds a scalar; keys past the sequence read zeros, and their
   // probabilities are 0.  The row goes into the vector offset, which the bound is checked against:
   // the scalar offset is taken off the bound first, and a ragged last block's would exceed it.
-  // The vector instructions bound the kernel - 28.6 to 22.8 million of them per launch at the
-  // shape above, 187 to 179 us - with the matrix cores busy 23% of the time.)
+  // The vector instructions bound the kernel: 28.6 to 22.8 million of them per launch so at the
+  // shape above, 187 to 179 us, and 20.6 million and 153 us with the mask's tests out of the
+  // passes' bodies; the matrix cores are busy 18% of the time.)
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
   u32x4 kreg[KPT], vreg[VPT][2];
   const int kld = (int)ldk * 2, vld = (int)ldv * 2;
@@ -667,23 +674,24 @@ __global__ void __launch_bounds__(256, 2) attention_gqa_kernel(const uint16_t* _
     fetch(last ? 0 : kb + 1, last);   // (after the last block the second pass's first)
     __syncthreads();
     if ((int64_t)kb * 64 > wq_last) continue;   // wave-uniform: this block is masked for all its queries
+    auto maxima = [&](auto mask_) {
+      constexpr bool MASK = decltype(mask_)::value;
+      int lim[QB];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      floatx4 st[QB];
-      scores_t(j, st);
+      for (int b = 0; b < QB; ++b) lim[b] = MASK ? key_limit(b, kb) : 0;
 #pragma unroll
-      for (int b = 0; b < QB; ++b) {
-        if (masked(b, kb)) {
-          const int lim = key_limit(b, kb);
+      for (int j = 0; j < 4; ++j) {
+        floatx4 st[QB];
+        scores_t(j, st);
+#pragma unroll
+        for (int b = 0; b < QB; ++b)
 #pragma unroll
           for (int i = 0; i < 4; ++i)
-            if (j * 16 + lk * 4 + i <= lim) mq[b] = fmaxf(mq[b], st[b][i]);
-        } else {
-#pragma unroll
-          for (int i = 0; i < 4; ++i) mq[b] = fmaxf(mq[b], st[b][i]);
-        }
+            mq[b] = fmaxf(mq[b], MASK && j * 16 + lk * 4 + i > lim[b] ? -INFINITY : st[b][i]);
       }
-    }
+    };
+    if (masked(kb)) maxima(std::true_type{});
+    else maxima(std::false_type{});
   }
   // exp(s * scale - max) = 2^(s * c - max * c) with c = scale * log2(e): one fma and the
   // hardware base-2 exponential per score; masked scores become -inf, whose 2^ is 0
@@ -714,36 +722,39 @@ __global__ void __launch_bounds__(256, 2) attention_gqa_kernel(const uint16_t* _
     // probabilities of the q-blocks as B operands: 32-key step c holds keys c*32 + 4*lk + i
     // (block j = 2c) and c*32 + 16 + 4*lk + i (block j = 2c + 1)
     bf16x8 pb[QB][2];
+    auto probabilities = [&](auto mask_) {
+      constexpr bool MASK = decltype(mask_)::value;
+      int lim[QB];
 #pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      uint32_t pw[QB][4];
+      for (int b = 0; b < QB; ++b) lim[b] = MASK ? key_limit(b, kb) : 0;
 #pragma unroll
-      for (int jj = 0; jj < 2; ++jj) {
-        const int j = 2 * c + jj;
-        floatx4 st[QB];
-        scores_t(j, st);
+      for (int c = 0; c < 2; ++c) {
+        uint32_t pw[QB][4];
 #pragma unroll
-        for (int b = 0; b < QB; ++b) {
-          if (masked(b, kb)) {
-            const int lim = key_limit(b, kb);
+        for (int jj = 0; jj < 2; ++jj) {
+          const int j = 2 * c + jj;
+          floatx4 st[QB];
+          scores_t(j, st);
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-              if (j * 16 + lk * 4 + i > lim) st[b][i] = -INFINITY;
+          for (int b = 0; b < QB; ++b) {
+            float p[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const float sc = MASK && j * 16 + lk * 4 + i > lim[b] ? -INFINITY : st[b][i];
+              p[i] = __builtin_amdgcn_exp2f(fmaf(sc, c2, -mc[b]));
+              lq[b] += p[i];
+            }
+            pw[b][2 * jj] = pack_bf16(p[0], p[1]);
+            pw[b][2 * jj + 1] = pack_bf16(p[2], p[3]);
           }
-          float p[4];
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            p[i] = __builtin_amdgcn_exp2f(fmaf(st[b][i], c2, -mc[b]));
-            lq[b] += p[i];
-          }
-          pw[b][2 * jj] = pack_bf16(p[0], p[1]);
-          pw[b][2 * jj + 1] = pack_bf16(p[2], p[3]);
         }
-      }
 #pragma unroll
-      for (int b = 0; b < QB; ++b)
-        pb[b][c] = __builtin_bit_cast(bf16x8, make_uint4(pw[b][0], pw[b][1], pw[b][2], pw[b][3]));
-    }
+        for (int b = 0; b < QB; ++b)
+          pb[b][c] = __builtin_bit_cast(bf16x8, make_uint4(pw[b][0], pw[b][1], pw[b][2], pw[b][3]));
+      }
+    };
+    if (masked(kb)) probabilities(std::true_type{});
+    else probabilities(std::false_type{});
     // A operand: V^T rows d = n*16 + lr, the same keys (two 8-byte reads per step)
 #pragma unroll
     for (int n = 0; n < ND; ++n)
