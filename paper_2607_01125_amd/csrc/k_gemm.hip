@@ -342,10 +342,16 @@ __device__ __forceinline__ void transpose4(floatx4& v) {
   v = floatx4{__uint_as_float(c[0]), __uint_as_float(c[1]), __uint_as_float(d[0]), __uint_as_float(d[1])};
 }
 
+// Four floats on any 4-byte boundary (global loads need no more).  Rows off 16 bytes read so, with
+// single elements only past the last whole four: 90 us as single elements throughout, 51 so, at
+// 8192 x 1000 outputs of depth 130.
+typedef floatx4 floatx4_a4 __attribute__((aligned(4)));
+
 // A wave owns 16 MI tokens x 32 features; a workgroup's four waves lie along the tokens (MI = 1)
 // or 2 x 2 (MI = 2).  The small tile is for few tokens and features: 64 x 64 tiles of scalar
-// multiply-adds left all but 2 to 16 compute units idle at 512 rows x 128-256 features (20-38 us
-// a call; now 4-8), and the chain order above keeps their bits.
+// multiply-adds left all but 2 to 16 compute units idle at 512 rows x 128-512 features (20-38 us
+// a call; now 7 to 9 at depth 128, 11 to 13 at 256, 19 to 21 at 512), and the chain order above
+// keeps their bits.
 template <int EPI, int MI>
 __global__ void __launch_bounds__(256) gemm_pm_f32_kernel(GemmArgsF32 a, int vec) {
   constexpr int TN = MI == 1 ? 32 : 64;
@@ -368,9 +374,11 @@ __global__ void __launch_bounds__(256) gemm_pm_f32_kernel(GemmArgsF32 a, int vec
     if (!in) return v;
     if (vec) {
       if (k < a.K) v = *reinterpret_cast<const floatx4*>(row + k);
+    } else if (k + 4 <= a.K) {
+      v = *reinterpret_cast<const floatx4_a4*>(row + k);
     } else {
 #pragma unroll
-      for (int s = 0; s < 4; ++s)
+      for (int s = 0; s < 3; ++s)
         if (k + s < a.K) v[s] = row[k + s];
     }
     return v;

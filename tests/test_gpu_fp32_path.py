@@ -34,6 +34,8 @@ def _dev(a, shift=0):
     (64, 128, 96, 17, Z.EPI_SWIGLU, True, False, 0),
     (17, 64, 128, 8, 0, False, True, 1),
     (1030, 96, 1000, 8, 0, True, True, 0),
+    (1030, 131, 1000, 8, 0, False, False, 1),
+    (40, 6, 48, 2, 0, False, False, 3),
 ])
 def test_linear_f32(T, K, N, r, flags, bias, resid, shift):
     announce("fp32 linear", T, K, N, r, flags, shift)
