@@ -126,9 +126,10 @@ struct TileGeom {
   int tm, tn, half;
   int64_t m0, n0;
 };
+template <bool TAIL>
 __device__ __forceinline__ TileGeom tile_geom(const GemmArgs& a, int ntiles, int v, bool shared) {
   const int tiles_m = shared ? a.tiles_m_half : 2 * a.tiles_m_half;   // (shared input: one half's tokens)
-  if (v >= a.tail_first) {   // split tail: feature tile columns past tiles_n - tail_cols, half 0's tiles first
+  if (TAIL && v >= a.tail_first) {   // split tail: feature tile columns past tiles_n - tail_cols, half 0's tiles first
     const int m = tail_m(a);
     TileGeom g;
     g.half = v - a.tail_first >= m ? 1 : 0;
@@ -140,10 +141,10 @@ __device__ __forceinline__ TileGeom tile_geom(const GemmArgs& a, int ntiles, int
     g.n0 = (int64_t)g.tn * 256;
     return g;
   }
-  ntiles = a.tail_first;     // the tiles before the tail: tiles_n - tail_cols feature columns
+  if (TAIL) ntiles = a.tail_first;   // the tiles before the tail: tiles_n - tail_cols feature columns
   int lin = v;
   if ((ntiles & 7) == 0) lin = (v & 7) * (ntiles >> 3) + (v >> 3);
-  const int per_group = 4 * (a.tiles_n - a.tail_cols);
+  const int per_group = 4 * (TAIL ? a.tiles_n - a.tail_cols : a.tiles_n);
   const int first_m = (lin / per_group) * 4;
   const int gsz = min(4, tiles_m - first_m);
   TileGeom g;
@@ -259,8 +260,10 @@ __device__ __forceinline__ void rank_correction_pre(const GemmArgs& a, const Til
 // + gridDim.x, ...  The stage ring runs on across tiles: the last two stages of a tile
 // load the next tile's stages 0 and 1, and its last sub-step reads the next tile's first
 // fragments, so the next tile starts without a prologue while this one finishes (rank
-// correction, epilogue straight from the accumulators, no LDS).
-template <int EPI, bool OUT_F32, bool SHARED>
+// correction, epilogue straight from the accumulators, no LDS).  TAIL: some of the launch's tiles
+// are cut by depth; a launch without a tail runs the kernel without that code (the branches cost
+// it about half a microsecond, 5% of the smallest calls).
+template <int EPI, bool OUT_F32, bool SHARED, bool TAIL>
 __global__ void __launch_bounds__(NT, 1) gemm_4w64_kernel(GemmArgs a, int ntiles) {
   constexpr bool PERM = epi_perm(EPI);
   extern __shared__ __align__(16) uint16_t lds[];
@@ -343,8 +346,8 @@ __global__ void __launch_bounds__(NT, 1) gemm_4w64_kernel(GemmArgs a, int ntiles
 
   int item = 0;
   VTile vt;
-  if (!vtile<epi_tail(EPI, SHARED)>(a, 0, NS, vt)) return;   // (uniform: more workgroups than whole tiles and shares)
-  TileGeom g = tile_geom(a, ntiles, vt.tile, SHARED);
+  if (!vtile<TAIL>(a, 0, NS, vt)) return;   // (uniform: more workgroups than whole tiles and shares)
+  TileGeom g = tile_geom<TAIL>(a, ntiles, vt.tile, SHARED);
   __amdgpu_buffer_rsrc_t xrs = buffer_rsrc(a.x + (int64_t)g.half * a.T * a.K, xbytes);
 
   // ---- prologue of the first tile: stages 0 and 1 in flight (slots 0..3), stage 0
@@ -391,8 +394,8 @@ __global__ void __launch_bounds__(NT, 1) gemm_4w64_kernel(GemmArgs a, int ntiles
     // iterations), so the compiler places no LDS waits inside it
     __builtin_amdgcn_s_waitcnt(WAIT_LGKM0);
     VTile vtn = vt;
-    const bool has_next = vtile<epi_tail(EPI, SHARED)>(a, item + 1, NS, vtn);
-    const TileGeom gn = tile_geom(a, ntiles, vtn.tile, SHARED);
+    const bool has_next = vtile<TAIL>(a, item + 1, NS, vtn);
+    const TileGeom gn = tile_geom<TAIL>(a, ntiles, vtn.tile, SHARED);
     const __amdgpu_buffer_rsrc_t xrs_n = buffer_rsrc(a.x + (int64_t)gn.half * a.T * a.K, xbytes);
 
     // ---- main loop: one stage (two sub-steps) per iteration.  Stages S + 2 past this
@@ -443,7 +446,7 @@ __global__ void __launch_bounds__(NT, 1) gemm_4w64_kernel(GemmArgs a, int ntiles
     // tile inside the plain feature range has none
     if (corr) rank_correction<PERM>(a, acc, fa1, fb1, g, p_half, c_half, wave, lane, pre, cpa, cpb);
 
-    if (epi_tail(EPI, SHARED) && vt.slot >= 0) {
+    if (TAIL && vt.slot >= 0) {
       // part of a tile: its accumulators to the split tail's slot, the epilogue runs later
       floatx4* slot = tail_slot(a, vt.slot, wave);
 #pragma unroll
@@ -486,7 +489,7 @@ __global__ void __launch_bounds__(NT) tail_combine_kernel(GemmArgs a, int ntiles
   int w1 = w0;
   while (tail_cut(a, w1 + 1, U) < (t + 1) * U) ++w1;
   if (w0 == w1) return;   // one share holds the whole tile and has written its outputs
-  const TileGeom g = tile_geom(a, ntiles, a.tail_first + tile, false);
+  const TileGeom g = tile_geom<true>(a, ntiles, a.tail_first + tile, false);
   const int64_t tok = g.m0 + (wave >> 1) * 128 + j * 16 + (lane & 15);
   const int64_t nw = g.n0 + (wave & 1) * 128;
   floatx4 v[8];
@@ -726,7 +729,7 @@ __global__ void __launch_bounds__(NT, 1) gemm_i4w64_kernel(GemmArgs a, int ntile
   using SubB = std::integral_constant<bool, true>;
 
   int v = blockIdx.x;
-  TileGeom g = tile_geom(a, ntiles, v, false);
+  TileGeom g = tile_geom<false>(a, ntiles, v, false);
   __amdgpu_buffer_rsrc_t xrs = buffer_rsrc(a.x + (int64_t)g.half * a.T * a.K, xbytes);
 
   // ---- prologue of the first tile: packed stages 0..2, x of stages 0 and 1; W of stage 0
@@ -771,7 +774,7 @@ __global__ void __launch_bounds__(NT, 1) gemm_i4w64_kernel(GemmArgs a, int ntile
     __builtin_amdgcn_s_waitcnt(WAIT_LGKM0);
     const int vn = v + (int)gridDim.x;
     const bool has_next = vn < ntiles;
-    const TileGeom gn = tile_geom(a, ntiles, has_next ? vn : v, false);
+    const TileGeom gn = tile_geom<false>(a, ntiles, has_next ? vn : v, false);
     const __amdgpu_buffer_rsrc_t xrs_n = buffer_rsrc(a.x + (int64_t)gn.half * a.T * a.K, xbytes);
 
     // ---- main loop: one stage per iteration.  Stages past this tile's end are the next
@@ -844,16 +847,24 @@ hipError_t launch_i4w64(const GemmArgs& a_in, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int EPI, bool OUT_F32, bool SHARED>
-hipError_t launch_4w64(const GemmArgs& a_in, hipStream_t s) {
-  GemmArgs a = a_in;
+template <int EPI, bool OUT_F32, bool SHARED, bool TAIL>
+hipError_t run_4w64(const GemmArgs& a, int ntiles, unsigned grid, hipStream_t s) {
   static bool attr_set = false;  // benign race: every thread sets the same value
   if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_4w64_kernel<EPI, OUT_F32, SHARED>),
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_4w64_kernel<EPI, OUT_F32, SHARED, TAIL>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
     if (e != hipSuccess) return e;
     attr_set = true;
   }
+  gemm_4w64_kernel<EPI, OUT_F32, SHARED, TAIL><<<dim3(grid), dim3(NT), LDS_BYTES, s>>>(a, ntiles);
+  if constexpr (TAIL)
+    tail_combine_kernel<EPI, OUT_F32><<<dim3((unsigned)((ntiles - a.tail_first) * 8)), dim3(NT), 0, s>>>(a, ntiles);
+  return hipGetLastError();
+}
+
+template <int EPI, bool OUT_F32, bool SHARED>
+hipError_t launch_4w64(const GemmArgs& a_in, hipStream_t s) {
+  GemmArgs a = a_in;
   const int ntiles = (SHARED ? 1 : 2) * a.tiles_m_half * a.tiles_n;
   const int ncu = cu_count();
   if (ncu <= 0) return hipErrorInvalidDevice;
@@ -867,12 +878,10 @@ hipError_t launch_4w64(const GemmArgs& a_in, hipStream_t s) {
   a.tail_first = ntiles - tp.cols * 2 * a.tiles_m_half;
   const int want = a.tail_first > tp.w ? a.tail_first : tp.w;
   const unsigned grid = (unsigned)(want < ncu ? want : ncu);
-  gemm_4w64_kernel<EPI, OUT_F32, SHARED><<<dim3(grid), dim3(NT), LDS_BYTES, s>>>(a, ntiles);
   if constexpr (TAIL) {
-    if (tp.w > 0)
-      tail_combine_kernel<EPI, OUT_F32><<<dim3((unsigned)((ntiles - a.tail_first) * 8)), dim3(NT), 0, s>>>(a, ntiles);
+    if (tp.w > 0) return run_4w64<EPI, OUT_F32, SHARED, true>(a, ntiles, grid, s);
   }
-  return hipGetLastError();
+  return run_4w64<EPI, OUT_F32, SHARED, false>(a, ntiles, grid, s);
 }
 
 }  // namespace

@@ -466,7 +466,7 @@ Choice choose(int64_t T, int64_t N, int64_t K, int64_t ws_bytes, int ncu) {
     const int64_t tiles = (nblk + nb - 1) / nb * tn;
     const int resident = (nb <= 8 ? 2 : 1) * ncu;
     const double bytes = 16384.0 + 2048.0 * nb;   // per workgroup and stage
-    for (int S = 1; S <= 16 && S * 4 <= NS; ++S) {
+    for (int S = 1; S <= 16 && (S == 1 || S * 4 <= NS); ++S) {   // (slices of at least 4 stages)
       const int64_t part = tiles * nb * 8192;
       if (S > 1 && (S + 1) * part > ws_bytes) break;
       const int64_t n = tiles * S;
