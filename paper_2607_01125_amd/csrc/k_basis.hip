@@ -1542,16 +1542,17 @@ static void mirror(float* g, int64_t n, hipStream_t s) {
 
 // G = X^T X through X^T and the plain bf16 GEMM (both halves of X^T's rows against all of them),
 // mirrored; xt_ws holds X^T (its rows padded with zeros to the GEMM's 64-deep stages) and, past it,
-// the GEMM's partial sums.  The triangle kernel
-// walks all tokens in each of its 128 x 128 tiles, 137 us at 4096 tokens however few tiles there
-// are, and 528 tiles (d = 4096) exceed two per compute unit: 275 us.  So 142 us there (transpose 12, GEMM 104,
-// mirror 25).
-// hipErrorNotSupported where the GEMM's 64-deep schedules do not cover the shape.
+// the GEMM's partial sums.  The triangle kernel walks all tokens in each of its 128 x 128 tiles,
+// 117 us at 4096 tokens however few tiles there are, and 528 tiles (d = 4096) exceed two per
+// compute unit: 268 us.  So 138 us there (transpose 12, GEMM 104, mirror 25), 22 against 37 at
+// 1024 x 512, 39 against 66 at 2048 x 2048.  Its four launches are the slower form only for a small
+// Gram of few tokens (19 against 10 us at 168 x 128, level at 512 x 128, 13 against 17 at 256 x 256).
+// hipErrorNotSupported there, and where the GEMM's 64-deep schedules do not cover the shape.
 hipError_t launch_gram_t(const uint16_t* x, int64_t n, int64_t d, int64_t ld, float* g, void* xt_ws, size_t bytes,
                          hipStream_t s) {
   const int64_t np = n <= 128 ? 128 : (n + 63) / 64 * 64;
   const size_t own = align256((size_t)np * d * 2);
-  if (n < 1 || d % 64 != 0 || bytes < own || own >= (size_t(1) << 31) || np > 65535 * 128)
+  if ((d < 256 && n < 512) || n < 1 || d % 64 != 0 || bytes < own || own >= (size_t(1) << 31) || np > 65535 * 128)
     return hipErrorNotSupported;
   uint16_t* xt = static_cast<uint16_t*>(xt_ws);
   transpose_bf16_kernel<<<dim3((unsigned)((np + 127) / 128), (unsigned)((d + 127) / 128)), 256, 0, s>>>(x, n, d, ld, np, xt);

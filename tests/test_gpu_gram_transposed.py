@@ -17,7 +17,19 @@ pytestmark = pytest.mark.gpu
     (200, 128, 128, 8), (100, 64, 64, 4), (1029, 1024, 1024, 16), (65536, 64, 64, 4),
 ])
 def test_basis_init_matches_gram(n, d, ld, r):
-    announce("gram transposed", n, d, ld, r)
+    _check(n, d, ld, r, 0)
+
+
+# both sides of the line to the triangle kernel (512 tokens below 256 features), ragged edges of the
+# transpose's tiles past it; fewer tokens than the block, X^T padded to the GEMM's least depth
+@pytest.mark.parametrize("n,d,ld,r,p", [(511, 64, 64, 4, 0), (512, 64, 72, 4, 0), (577, 192, 200, 8, 0),
+                                        (300, 256, 256, 8, 0), (100, 256, 264, 4, 100)])
+def test_basis_init_matches_gram_at_the_line(n, d, ld, r, p):
+    _check(n, d, ld, r, p)
+
+
+def _check(n, d, ld, r, p):
+    announce("gram transposed", n, d, ld, r, p)
     g = torch.Generator(device=dev())
     g.manual_seed(n + d)
     k = min(2 * r, d)
@@ -27,7 +39,7 @@ def test_basis_init_matches_gram(n, d, ld, r):
     wide[:, :d] = ((torch.randn(n, k, generator=g, device=dev()) * s * 8) @ q.T
                    + 0.01 * torch.randn(n, d, generator=g, device=dev())).to(torch.bfloat16)
     x = wide[:, :d]
-    opts = Z.EigOpts(0, 40, 0x5EED, 0.0, 0, 0)
+    opts = Z.EigOpts(p, 40, 0x5EED, 0.0, 0, 0)
     out = []
     for one in (True, False):
         ut = torch.full((r, d), float("nan"), device=dev())
