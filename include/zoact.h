@@ -77,7 +77,9 @@ enum {
                                  once and each half adds its own rank-r correction
                                  to it (the same operations in the same order as
                                  with the input given twice, so the outputs are
-                                 the same bits).  BF16 weights with L->ch (or
+                                 the same bits, save where L->ws lets the call with
+                                 the input given twice split a partly idle last
+                                 round by depth).  BF16 weights with L->ch (or
                                  r == 0), d_in % 64 == 0 and >= 128; not with
                                  ZOACT_EPI_SWIGLU.  Else ZOACT_E_UNSUPPORTED.      */
 };
@@ -146,8 +148,11 @@ typedef struct {
                            tiles than compute units, spread over them by depth where that
                            is faster (for example 160 or 640 tiles on 256 compute units;
                            BF16 weights without ZOACT_SHARED_X).  Other summation
-                           order than without ws, same bits in both halves of the pair.
-                           NULL: not used.  Calls that overlap on one workspace race.    */
+                           order than without ws, same bits in both halves of the pair;
+                           in the first case also the same bits from INT4 weights as
+                           from their bf16 values.  NULL: not used.  Calls that overlap
+                           on one workspace race: layers used on several streams at once,
+                           of whatever type and epilogue, need a workspace per stream.   */
   size_t ws_bytes;
 } zoact_linear;
 
@@ -423,9 +428,13 @@ zoact_status zoact_step_q_sgd(const zoact_arena* A, const float* losses, int32_t
  *   (device, nullable; see zoact_eig_report).  Iteration control and synchronisation:
  *   see zoact_eig_opts.  Workspace: ws of at least zoact_basis_workspace_bytes(d, r,
  *   opts) bytes.
- * zoact_basis_init: zoact_gram followed by zoact_basis_from_gram, with g at the
- *   start of ws; ws needs zoact_basis_init_workspace_bytes(d, r, opts) bytes (the
- *   Gram d*d fp32, padded to 256 bytes, then the solver's workspace).  With fewer
+ * zoact_basis_init: the Gram, at the start of ws, followed by zoact_basis_from_gram;
+ *   ws needs zoact_basis_init_workspace_bytes(d, r, opts) bytes (the Gram d*d fp32,
+ *   padded to 256 bytes, then the solver's workspace).  For BF16 x whose transpose
+ *   (n_tok rounded up to 64, at least 128, times d values) fits in ws past the Gram,
+ *   with d >= 256 or n_tok >= 512, the Gram's fp32 sums run in another order than
+ *   zoact_gram's; what fits, and so the last bits, depends on ws_bytes (a caller that
+ *   wants the same bits passes the same size).  With fewer
  *   rows than features (BF16 x, n_tok < d, r + p <= n_tok, d % 64 == 0, ld_x % 8 ==
  *   0, x 16-byte aligned) and ws also large enough for it, the same singular vectors
  *   come from the thin SVD's other side (Section 3): the solver runs on the

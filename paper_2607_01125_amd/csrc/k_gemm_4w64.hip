@@ -546,7 +546,7 @@ TailPlan plan_tail(int tiles_mh, int tiles_n, int NS, int64_t ws_bytes, int ncu)
 // row of the tile (wave * 64 + lane): it reads its packed half rows and writes bf16(q * s)
 // into a bf16 W tile, the values zoact_dequant_int4 forms, so the fragments, MFMAs, rank
 // correction and epilogue are those of the bf16 schedule with the dequantised weight (its
-// results are the same bits).  A wave converts the rows it loaded itself, so the packed
+// results are the same bits as that schedule's whole tiles; it splits no tail).  A wave converts the rows it loaded itself, so the packed
 // ring needs no barrier; the conversion of a stage is spread, four values (half a 16-byte
 // chunk) per row of MFMAs, over the two sub-steps before the barrier that publishes it.
 //

@@ -10,8 +10,8 @@
 //    short batch and W crosses L2 -> LDS once for them;
 //  * the depth is split over S workgroups (slices of whole 64-deep stages); each stores its
 //    fp32 accumulators, and a second kernel adds the slices in the order 0 .. S - 1 and runs
-//    the epilogue.  The slices depend on (T, N, K) only, so the halves, the shared-input
-//    form and the INT4 form of a call give the same bits as each other;
+//    the epilogue.  The slices depend on (T, N, K) and the workspace only, so the halves, the
+//    shared-input form and the INT4 form of a call give the same bits as each other;
 //  * 64-deep stages through LDS: three 16 KB W slots and two x slots (80 KB at NB = 8), so two
 //    workgroups share a CU and hide each other's waits.  W of stage S + 2 is requested during
 //    the first sub-step of stage S, x of S + 2 during the second, one barrier per stage.
@@ -19,12 +19,17 @@
 //    registers of the one wave that multiplies them.
 //
 // What bounds it: at 16 to 64 tokens the W bytes from HBM; above, the L2 -> LDS rate (13 to 14
-// TB/s over the chip whatever the occupancy, ring depth or store kind).  Measured against the
-// 256 x 256 schedule (us, bf16, 16 / 64 / 256 / 1024 tokens per half):
-//   q|k|v 4096 -> 6144    15 / 19 / 37 / 84     was 74 / 73 / 75 / 84
-//   o 4096 -> 4096        14 / 16 / 28 / 64     was 75 / 74 / 78 / 82
-//   down 14336 -> 4096    30 / 41 / 76 / 223    was 243 / 245 / 295 / 290
-//   fc2 20480 -> 5120     48 / 64 / 121 / 511   was 413 / 422 / 581 / 551
+// TB/s over the chip whatever the occupancy, ring depth or store kind).  Measured with a workspace
+// and weights from HBM against the 256 x 256 schedule with its split tail (us, bf16, 16 / 64 / 256
+// / 512 / 768 / 1024 tokens per half; "=": that schedule is the one chosen):
+//   q|k|v 4096 -> 6144    18 / 23 / 43 / 58 / 81 / =        42 / 42 / 46 / 74 / 82 / 87
+//   o 4096 -> 4096        16 / 19 / 31 / 43 / 59 / 65       36 / 37 / 39 / 52 / 72 / 76
+//   gate|up 4096 -> 28672 56 / 62 / = / = / = / =           88 / 91 / 102 / 200 / 287 / 371
+//   down 14336 -> 4096    38 / 42 / 69 / 118 / 182 / 211    65 / 65 / 74 / 110 / 158 / 191
+//   out 5120 -> 5120      23 / 30 / 43 / 86 / 80 / =        42 / 43 / 49 / 78 / 96 / 101
+//   fc2 20480 -> 5120     66 / 69 / 115 / 307 / 290 / =     117 / 119 / 138 / 220 / 329 / 382
+// and INT4 against its whole tiles: o 19 / 24 / 38 / 56 / 81 / 82 (101 to 106 throughout), down 42 /
+// 42 / 81 / 143 / 253 / 262 (331 to 336).
 #include <algorithm>
 #include <type_traits>
 
@@ -443,8 +448,10 @@ hipError_t launch_s(const GemmArgs& a, const SPlan& pl, hipStream_t s) {
 //
 // The line between the schedules, and the slices, come from the time each form is bound by, in
 // bytes per microsecond, fitted to a sweep over the Llama-3-8B and OPT-13B layer shapes at 16 to
-// 2048 tokens per half (96 shapes; the choice is within 4% of the best variant on average, and
-// never slower than the 256 x 256 schedule):
+// 2048 tokens per half (96 shapes).  The other side of the line is that schedule's whole tiles
+// (1.2 us a stage): its split tail, which a workspace allows with bf16 weights, is not priced, and
+// from about 512 tokens per half it is the faster form at some shapes that are kept here (the table
+// above: down at 512 to 1024, out and fc2 at 512).  INT4 weights are charged as bf16 bytes:
 //  * one workgroup moves at most 55 KB/us from L2 to LDS, all of them 14 TB/s (the L2 rate, which
 //    also bounds the 256 x 256 schedule: 64 KB per 1.2 us stage and CU), and W comes from HBM at
 //    5 TB/s;

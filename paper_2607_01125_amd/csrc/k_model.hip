@@ -6,12 +6,11 @@
 // (64-query block, head, sequence), scores and P.V on v_mfma_f32_16x16x32_bf16, a
 // two-pass softmax in fp32 with wave64 shuffles, K and V staged through LDS (V
 // transposed so that each lane's fragment holds 8 consecutive keys).
-#include <type_traits>
-
 #include <math.h>
 #include <stdio.h>
 
 #include <string>
+#include <type_traits>
 
 #include "common.hpp"
 #include "zoact_model.h"
