@@ -135,9 +135,16 @@ __device__ __forceinline__ TileGeom tile_geom(const GemmArgs& a, int ntiles, int
     g.half = v - a.tail_first >= m ? 1 : 0;
     const int t0 = v - a.tail_first - g.half * m, per = m / a.tail_g;
     const int t = (t0 % per) * a.tail_g + t0 / per;   // tiles at the same place of their repeat are neighbours
-    g.tm = t % a.tiles_m_half + g.half * a.tiles_m_half;
-    g.tn = a.tiles_n - a.tail_cols + t / a.tiles_m_half;
-    g.m0 = (int64_t)(t % a.tiles_m_half) * 256;
+    // (groups of at most eight token tiles, feature tiles inside, so that an XCD's neighbours read
+    // few rows of x: at 16 token tiles per half 5120 x 5120 ran 314 to 320 us with all of them in
+    // a row, 307 so, 5120 x 20480 1453 and 1433; groups of four were 2 to 3% slower at 5 to 8)
+    const int ng = (a.tiles_m_half + 7) >> 3, gm = (a.tiles_m_half + ng - 1) / ng;
+    const int per_group = gm * a.tail_cols, first_m = t / per_group * gm;
+    const int gsz = min(gm, a.tiles_m_half - first_m);
+    const int tm = first_m + t % per_group % gsz;
+    g.tm = tm + g.half * a.tiles_m_half;
+    g.tn = a.tiles_n - a.tail_cols + t % per_group / gsz;
+    g.m0 = (int64_t)tm * 256;
     g.n0 = (int64_t)g.tn * 256;
     return g;
   }
@@ -512,10 +519,11 @@ __global__ void __launch_bounds__(NT) tail_combine_kernel(GemmArgs a, int ntiles
 // A partial sum's way out and back is about 0.1 us per 256 KB slot over the chip (measured 160
 // slots: 17 us, 416: 28 us in the second launch, the stores 6 to 12 more) against 1.35 us per
 // stage, so w = sqrt(R NS 1.35 / 0.09) workgroups balance the two, at most one per compute unit
-// and at least one per tile.  Split only where that leaves 8% of the launch, and up to 0.65 tiles
-// per compute unit: the clock falls as the chip fills (fc2: 1.5 us a stage with 160 busy compute
-// units, 1.9 with all), so 200 and 240 tiles ran 557 and 583 us split, 478 and 542 whole; 160
-// tiles 430 split, 524 whole.
+// and at least one per tile.  Split where that comes out shorter (near the line, at 0.90 to 1.0 of
+// the whole tiles' time as estimated, ten shapes measured 0.95 to 1.0), and up to 0.65 tiles per
+// compute unit: the clock falls as the chip fills (fc2: 1.5 us a stage with 160 busy compute units,
+// 1.9 with all), so 200 and 240 tiles ran 557 and 583 us split, 478 and 542 whole; 160 tiles 430
+// split, 524 whole.
 struct TailPlan {
   int w, cols;
 };
@@ -535,7 +543,7 @@ TailPlan plan_tail(int tiles_mh, int tiles_n, int NS, int64_t ws_bytes, int ncu)
   if (w <= R) return {0, 0};
   const double rounds = ntiles / ncu, c = 1.35;
   const double whole = (rounds + 1) * NS * c, split = (rounds * NS + (double)R * NS / w) * c + 0.09 * (w % R ? w + R : w) + 4.0;
-  return split < 0.92 * whole ? TailPlan{w, R / tiles_m} : TailPlan{0, 0};
+  return split < whole ? TailPlan{w, R / tiles_m} : TailPlan{0, 0};
 }
 
 // ---------------------------------------------------------------------------------------

@@ -22,7 +22,7 @@
 // TB/s over the chip whatever the occupancy, ring depth or store kind).  Measured with a workspace
 // and weights from HBM against the 256 x 256 schedule with its split tail (us, bf16, 16 / 64 / 256
 // / 512 / 768 / 1024 tokens per half; "=": that schedule is the one chosen):
-//   q|k|v 4096 -> 6144    18 / 23 / 43 / 58 / 81 / =        42 / 42 / 46 / 74 / 82 / 87
+//   q|k|v 4096 -> 6144    18 / 23 / 43 / 58 / = / =         42 / 42 / 46 / 74 / 82 / 87
 //   o 4096 -> 4096        16 / 19 / 31 / 43 / 59 / 65       36 / 37 / 39 / 52 / 72 / 76
 //   gate|up 4096 -> 28672 56 / 62 / = / = / = / =           88 / 91 / 102 / 200 / 287 / 371
 //   down 14336 -> 4096    38 / 42 / 69 / 118 / 182 / 211    65 / 65 / 74 / 110 / 158 / 191

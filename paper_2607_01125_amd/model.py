@@ -209,8 +209,8 @@ class Decoder:
         # largest layer's size, allocated on first use) and runs the bf16 schedule, from more
         # than INT4_PACKED_MAX_TOKENS tokens per half; False always keeps the GEMMs that read
         # the packed weights.  The same bits either way, save where the bf16 schedule splits a
-        # partly idle last round by depth, which the packed one does not (OPT fc2 from 769 to
-        # 1024 tokens per half).  Four Llama-3-8B projections of a
+        # partly idle last round by depth, which the packed one does not (gate|up of
+        # Llama-3-8B, fc2 of OPT-13B from 769 to 1024 tokens per half).  Four Llama-3-8B projections of a
         # layer on MI355X, packed against pass + bf16 GEMM: 128 us against 198 at 16 tokens
         # per half, 208 / 281 at 128, 304 / 334 at 256, 530 / 492 at 512, 1580 / 1347 at
         # 2048: the packed GEMMs convert every weight once per token tile, the pass once per

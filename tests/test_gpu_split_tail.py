@@ -23,6 +23,7 @@ pytestmark = pytest.mark.gpu
     (1000, 1600, 9216, 0, 0, False, False, True),
     (512, 8128, 25600, 32, 0, False, False, True),
     (1000, 20480, 5120, 64, 0, True, True, True),
+    (2200, 8192, 2304, 8, 0, False, True, True),   # nine token tiles per half: groups of five and four
     (500, 1088, 33328, 32, 0, True, True, False),
     (500, 1088, 33312, 8, Z.EPI_SWIGLU, True, False, False),
     (500, 1088, 33328, 16, Z.EPI_RELU, True, True, False),
