@@ -88,17 +88,23 @@ __global__ void __launch_bounds__(256) adam_kernel(void* __restrict__ cptr, floa
     if (!NEXT) return;
   }
   // next perturbation of arena indices 4b .. 4b + nl - 1 from their stored values cs: a whole
-  // block in two 8-byte stores when both halves' rows stay 8-byte aligned (k % 4 == 0)
+  // block in one 8-byte store per half where the half's row is 8-byte aligned (half 1: k % 4 == 0)
   const bool vec_out = (k & 3) == 0;
   auto next_pert = [&](int64_t b, const float* cs, int nl) {
     const float4 za = rng::gauss_block(nx.seed, nx.step, nx.query[0], (uint64_t)b);
     const float4 zb = nx.query[0] == nx.query[1] ? za : rng::gauss_block(nx.seed, nx.step, nx.query[1], (uint64_t)b);
-    if (nl == 4 && vec_out) {
+    if (nl == 4) {
       const int64_t e = 4 * b;
       st4_bf16_nt(out + e, pert_one(cs[0], nx.eps * za.x, nx.sign[0]), pert_one(cs[1], nx.eps * za.y, nx.sign[0]),
                   pert_one(cs[2], nx.eps * za.z, nx.sign[0]), pert_one(cs[3], nx.eps * za.w, nx.sign[0]));
-      st4_bf16_nt(out + k + e, pert_one(cs[0], nx.eps * zb.x, nx.sign[1]), pert_one(cs[1], nx.eps * zb.y, nx.sign[1]),
-                  pert_one(cs[2], nx.eps * zb.z, nx.sign[1]), pert_one(cs[3], nx.eps * zb.w, nx.sign[1]));
+      const float o[4] = {pert_one(cs[0], nx.eps * zb.x, nx.sign[1]), pert_one(cs[1], nx.eps * zb.y, nx.sign[1]),
+                          pert_one(cs[2], nx.eps * zb.z, nx.sign[1]), pert_one(cs[3], nx.eps * zb.w, nx.sign[1])};
+      if (vec_out) {
+        st4_bf16_nt(out + k + e, o[0], o[1], o[2], o[3]);
+      } else {
+#pragma unroll
+        for (int l = 0; l < 4; ++l) out[k + e + l] = f2bf(o[l]);
+      }
       return;
     }
     for (int l = 0; l < nl; ++l) {
