@@ -133,3 +133,9 @@ def test_pair_and_query_step_validation():
     # the two-sided pair written as a general pair is accepted (fails later only for want of a GPU)
     good = Z.pert_pair(1, 1, (0, 0), (1, -1), 1e-3)
     assert tuple(good.sign) == (1, -1) and tuple(good.query) == (0, 0)
+
+
+def test_project_part_needs_the_whole_batch_to_hold_its_rows():
+    L, p = Z.lib(), ctypes.c_void_p(16)
+    assert L.zoact_project_part(p, Z.BF16, 8, 7, 64, p, 8, p, None, 0, None) == Z.E_INVALID
+    assert b"n_all=7" in L.zoact_last_error()

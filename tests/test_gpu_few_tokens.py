@@ -54,6 +54,8 @@ def _want(x, w, b, p, ch, r, T, plain, flags, res):
 @pytest.mark.parametrize("T,K,N,r,flags,bias,resid,plain,out_f32", [
     (1, 128, 144, 8, 0, True, True, (0, 0), False),          # one token, two stages
     (20, 192, 272, 16, Z.EPI_RELU, True, False, (0, 0), False),   # three stages
+    (200, 128, 1552, 8, 0, True, True, (0, 0), False),       # two stages, larger tiles
+    (300, 192, 4096, 32, Z.EPI_SWIGLU, False, False, (0, 0), False),
     (16, 512, 128, 32, 0, False, False, (0, 0), False),      # whole blocks: one 32-row tile
     (17, 1024, 4096, 64, Z.EPI_RELU, True, False, (0, 0), False),
     (33, 2048, 1040, 5, 0, True, True, (0, 0), False),       # odd rank: element-wise correction
